@@ -231,6 +231,11 @@ lbm_status lbm_set_launch(lbm_handle *h, int32_t block_x, int32_t seg_rows);
  * alignment) and seg_rows (>= 1) set the two-step launch shape; 0 keeps the
  * library's choice (256 threads; segments of 2..40 rows, as many as fill whole
  * rounds of the workgroups the device runs at once).  lbm_init selects 2.
+ * With 2 and neither block_x nor seg_rows given, lbm_step may take more than
+ * two steps per launch while enough steps are left (four in the deep pass);
+ * pairs and an odd remainder follow in the forms above.  The results and the
+ * first domain error are the same, bitwise.  A shape given here is used for
+ * every pair of steps.
  * Batches have their own setting (lbm_batch_set_fusion). */
 lbm_status lbm_set_fusion(lbm_handle *h, int32_t steps, int32_t block_x, int32_t seg_rows);
 
@@ -238,8 +243,8 @@ lbm_status lbm_set_fusion(lbm_handle *h, int32_t steps, int32_t block_x, int32_t
 int32_t lbm_get_fusion(const lbm_handle *h);
 
 /* The launch shape of the step kernel in use (the two-step pass's when
- * lbm_get_fusion is 2): out[0] = block_x, out[1] = seg_rows, out[2] =
- * workgroups per launch. */
+ * lbm_get_fusion is 2, also where longer passes are taken before it): out[0] =
+ * block_x, out[1] = seg_rows, out[2] = workgroups per launch. */
 lbm_status lbm_get_launch(const lbm_handle *h, int32_t out[3]);
 
 /* Pick the step kernel's launch shape by measurement: time a few launches for
@@ -247,9 +252,11 @@ lbm_status lbm_get_launch(const lbm_handle *h, int32_t out[3]);
  * 3..17 rows; two-step pass, when lbm_get_fusion is 2: widths 128, 256, 512,
  * each with its default segment length and segments of 12..48 rows) and keep
  * the fastest per time step, switching to single steps if they win (results
- * are bitwise the same; lbm_get_fusion tells which).  The timed launches
- * write only the spare population buffer and are not counted as steps, so
- * the state and t are unchanged.  Synchronous; out (may be NULL) receives the
+ * are bitwise the same; lbm_get_fusion tells which).  Passes of more than two
+ * steps are timed at the library's shape and used while they are the fastest;
+ * the shape reported is then the two-step pass's, for the steps they leave.
+ * The timed launches write only the spare population buffer and are not
+ * counted as steps, so the state and t are unchanged.  Synchronous; out (may be NULL) receives the
  * chosen block_x, seg_rows and the measured microseconds per time step. */
 lbm_status lbm_autotune(lbm_handle *h, double out[3]);
 
@@ -259,9 +266,9 @@ lbm_status lbm_autotune(lbm_handle *h, double out[3]);
  * stream, all with the same storage mode, force_on and collision, any sizes
  * and any other parameters.  lbm_batch_step launches one kernel per two time
  * steps (the two-step pass; one per step after lbm_batch_set_fusion(b, 1),
- * and for an odd last step) covering every tile
- * of every lattice (a workgroup finds its lattice in a device table), and
- * replays a captured HIP graph of eight steps for every full eight steps of a
+ * and for an odd last step; or one per four steps, as lbm_step does, until a
+ * launch shape is set) covering every tile of every lattice (a workgroup
+ * finds its lattice in a device table), and replays a captured HIP graph of eight steps for every full eight steps of a
  * call (not on the legacy null stream, which cannot be captured: there each
  * launch is made on its own).  Each lattice keeps its own workspace, state,
  * time counter and sticky error word, so lbm_moments, lbm_diagnostics,
@@ -315,8 +322,9 @@ int32_t lbm_batch_get_fusion(const lbm_batch *b);
 /* Fix the batch's launch: `steps` per launch (1 or 2) with workgroups of
  * block_x threads walking segments of seg_rows rows.  Two-step pass: block_x
  * 128, 256 or 512, seg_rows >= 1, or 0 for the length chosen at each table
- * upload (as before lbm_batch_autotune).  Single steps: block_x a multiple of
- * 64 in 64..512, seg_rows >= 1.  Other values: LBM_ERR_INVALID_ARG, nothing
+ * upload (as before lbm_batch_autotune); every pair of steps is then taken in
+ * that form, and longer passes are not used.  Single steps: block_x a multiple
+ * of 64 in 64..512, seg_rows >= 1.  Other values: LBM_ERR_INVALID_ARG, nothing
  * changed.  For callers that have measured a shape (lbm_batch_autotune) and
  * want it again without the timing, and for profiling runs that must launch
  * one known shape.  Results are bitwise the same for every shape.  The next

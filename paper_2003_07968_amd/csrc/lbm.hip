@@ -82,6 +82,9 @@ struct lbm_handle {
     int cus;                 // compute units of the device (default shapes)
     int bx2, seg_rows2;      // launch shape of the two-step pass
     Tiles tiles2;
+    bool deep;               // the deep pass is used for whole groups of kDeepSteps steps
+    int bxd, seg_rowsd;      // its launch shape
+    Tiles tilesd;
     int device;              // HIP device current at lbm_init
     lbm_status sticky;
     std::string last_error;
@@ -141,7 +144,9 @@ struct lbm_batch {
     int bx, rows;             // single-step shape
     int bx2, rows2;           // two-step shape
     bool auto_rows2;          // rows2 chosen at each upload (until autotuned)
-    int total_tiles, total_tiles2;
+    bool deep;                // the deep pass may be used (no shape was asked for)
+    int bxd, rowsd;           // its shape, chosen at each upload
+    int total_tiles, total_tiles2, total_tilesd;  // total_tilesd 0: not used
     hipGraphExec_t graph;     // kGraphSteps batched steps, valid with the table
     bool graph_valid;
     std::string last_error;
@@ -149,6 +154,7 @@ struct lbm_batch {
 
 namespace {
 
+constexpr int kHaloD = 2 * kDeepSteps - 1;
 constexpr int kGraphSteps = 8;    // even: a multiple of the steps per launch
 constexpr int kBatchRows2 = 24;   // segment rows of the two-step pass in a batch
 const int kBatchRowsCand2[] = {2, 3, 4, 6, 8, 12, 16, 20, 24, 32, 40};
@@ -386,6 +392,111 @@ bool default_rows2(int nx, int ny, int storage, int bx, int cus, int *rows, Tile
     }
 }
 
+// Tiles of the deep pass: kHaloD halo columns on each side of a strip, strips
+// of a multiple of 16 columns as in the two-step pass.
+int deep_width(int nx, int bx)
+{
+    const int w = bx - 2 * kHaloD;
+    return nx > w ? w / 16 * 16 : nx;
+}
+
+bool make_tilesd(int nx, int ny, int bx, int seg_rows, Tiles *tl)
+{
+    const int w = deep_width(nx, bx);
+    tl->width = w;
+    tl->nstrips = (nx + w - 1) / w;
+    tl->nseg = (ny + seg_rows - 1) / seg_rows;
+    const long long nt = (long long)tl->nstrips * tl->nseg;
+    if (nt > kMaxTiles) return false;
+    tl->ntiles = (int)nt;
+    return true;
+}
+
+// Launch shape of the deep pass for a set of lattices (one, or a batch's
+// members): the columns per step (64, 128 or 256) and the segment length that
+// minimise
+//     rounds x (rows + kDeepFill) x t(lanes in use per CU).
+// A CU runs kDeepSteps x 256 threads at once (twice that with FP32 and FP16
+// storage, whose kernels fit 64 registers), or as many in narrower
+// workgroups; an iteration of a CU that is filled to the fraction u takes
+// t = max(0.4, 0.16 + 0.84 u) of a full one (2048^2-type lattices: FP32 0.95
+// us with one workgroup per CU, 1.63 us with two; a lone narrow workgroup is
+// bound by latency).  kDeepFill: a walk takes 21 iterations more than its
+// rows, in which part of the steps are idle.
+constexpr int kDeepFill = 16;
+const int kDeepRowsCand[] = {2,  3,  4,  5,  6,  8,  10, 12,  14,  16,  20,  24,  28,  32,  37,  42,
+                             48, 56, 64, 74, 84, 96, 110, 128, 147, 170, 196, 220, 256, 293, 341, 400};
+
+int deep_wgs_per_cu(int storage, int bx)
+{
+    const bool two = storage == LBM_STORE_F32_SHIFTED || storage == LBM_STORE_F16_SHIFTED;
+    return (two ? 2 : 1) * 256 / bx;
+}
+
+// Sizes and strip counts of the lattices a shape is chosen for.
+struct DeepSizes {
+    const int32_t *nx, *ny;
+    int count, stride;  // the sizes of lattice k are at nx[k stride], ny[k stride]
+};
+
+// Cost of one launch in units of a full CU's iteration; strips[k] strips in
+// lattice k.  Negative if a lattice needs too many tiles.
+double deep_cost(const DeepSizes &z, const int *strips, int storage, int cus, int bx, int rows)
+{
+    long long tiles = 0;
+    for (int k = 0; k < z.count; ++k) {
+        const unsigned ny = (unsigned)z.ny[(size_t)k * z.stride], r = std::min((unsigned)rows, ny);
+        const long long t = (long long)strips[k] * ((ny + r - 1) / r);
+        if (t > kMaxTiles) return -1.0;
+        tiles += t;
+    }
+    const int per_cu = deep_wgs_per_cu(storage, bx);
+    const long long slots = (long long)per_cu * cus, full = tiles / slots, rest = tiles % slots;
+    const double u = (double)((rest + cus - 1) / cus) / per_cu;
+    const double last = rest ? std::max(0.4, 0.16 + 0.84 * u) : 0.0;
+    return ((double)full + last) * (rows + kDeepFill);
+}
+
+bool deep_shape(const DeepSizes &z, int storage, int cus, int *bx, int *rows)
+{
+    double best = -1.0;
+    std::vector<int> many((size_t)(z.count > 1 ? z.count : 0));
+    int one, *strips = z.count > 1 ? many.data() : &one;
+    for (int b : {256, 128, 64}) {
+        int total = 0;
+        for (int k = 0; k < z.count; ++k) {
+            const int nx = z.nx[(size_t)k * z.stride], w = deep_width(nx, b);
+            strips[k] = (nx + w - 1) / w;
+            total += strips[k];
+        }
+        auto consider = [&](int r) {
+            const double cost = deep_cost(z, strips, storage, cus, b, r);
+            if (cost >= 0.0 && (best < 0.0 || cost < best)) {
+                best = cost;
+                *bx = b;
+                *rows = r;
+            }
+        };
+        for (int r : kDeepRowsCand)
+            consider(r);
+        // lengths that cut lattices of the first one's size into whole rounds
+        for (int half = 1; half <= 8; ++half) {
+            const int slots = deep_wgs_per_cu(storage, b) * cus;
+            const int nseg = std::max(1, half * slots / 2 / total), ny = z.ny[0];
+            consider(std::max(2, (ny + nseg - 1) / nseg));
+        }
+    }
+    return best >= 0.0;
+}
+
+bool default_deep(const lbm_params &p, int cus, int *bx, int *rows, Tiles *tl)
+{
+    if (!p.force_on) return false;
+    if (!deep_shape(DeepSizes{&p.nx, &p.ny, 1, 0}, p.storage, cus, bx, rows)) return false;
+    *rows = std::min(*rows, (int)p.ny);
+    return make_tilesd(p.nx, p.ny, *bx, *rows, tl);
+}
+
 // Compute units of the current device (256 on MI355X if the query fails).
 int device_cus()
 {
@@ -442,6 +553,21 @@ hipError_t run_sweep2(lbm_handle *h, const void *src, void *dst)
     return hipErrorInvalidValue;
 }
 
+// kDeepSteps time steps in one pass.
+hipError_t run_deep(lbm_handle *h, const void *src, void *dst)
+{
+    SweepArgs a = sweep_args(h, src, dst, Fields{}, true);
+    a.tl = h->tilesd;
+    a.bx = h->bxd;
+    switch (h->c.storage) {
+    case LBM_STORE_F64: return launch_deep<LBM_STORE_F64>(a);
+    case LBM_STORE_F32_SHIFTED: return launch_deep<LBM_STORE_F32_SHIFTED>(a);
+    case LBM_STORE_F16_SHIFTED: return launch_deep<LBM_STORE_F16_SHIFTED>(a);
+    case LBM_STORE_F16_LOCAL: return launch_deep<LBM_STORE_F16_LOCAL>(a);
+    }
+    return hipErrorInvalidValue;
+}
+
 hipError_t run_init(lbm_handle *h, const double *rho0, const double *ux0, const double *uy0)
 {
     switch (h->c.storage) {
@@ -492,28 +618,38 @@ lbm_status read_sticky(lbm_handle *h)
 }
 
 
-BatchArgs batch_args(const lbm_batch *b, bool two, const long long *ctr, long long steps_add,
+BatchArgs batch_args(const lbm_batch *b, int steps, const long long *ctr, long long steps_add,
                      int launches_add)
 {
+    const bool two = steps == 2, deep = steps == kDeepSteps;
     return BatchArgs{b->d_table,
                      (int)b->members.size(),
                      ctr,
                      steps_add,
                      launches_add,
-                     two ? b->bx2 : b->bx,
-                     (unsigned)(two ? b->total_tiles2 : b->total_tiles),
+                     deep ? b->bxd : (two ? b->bx2 : b->bx),
+                     (unsigned)(deep ? b->total_tilesd : (two ? b->total_tiles2 : b->total_tiles)),
                      b->force_on,
                      b->coll,
                      b->stream};
 }
 
-// One batched launch of `steps` (1 or 2) steps starting where batch_pos says:
+// One batched launch of `steps` (1, 2 or kDeepSteps) steps starting where batch_pos says:
 // eager launches pass the position (ctr = nullptr), captured ones their offset
 // from the device counters.
 hipError_t batch_launch_steps(lbm_batch *b, int steps, const long long *ctr, long long steps_add,
                               int launches_add)
 {
-    const BatchArgs a = batch_args(b, steps == 2, ctr, steps_add, launches_add);
+    const BatchArgs a = batch_args(b, steps, ctr, steps_add, launches_add);
+    if (steps == kDeepSteps) {
+        switch (b->storage) {
+        case LBM_STORE_F64: return launch_batch_deep<LBM_STORE_F64>(a);
+        case LBM_STORE_F32_SHIFTED: return launch_batch_deep<LBM_STORE_F32_SHIFTED>(a);
+        case LBM_STORE_F16_SHIFTED: return launch_batch_deep<LBM_STORE_F16_SHIFTED>(a);
+        case LBM_STORE_F16_LOCAL: return launch_batch_deep<LBM_STORE_F16_LOCAL>(a);
+        }
+        return hipErrorInvalidValue;
+    }
     if (steps == 2) {
         switch (b->storage) {
         case LBM_STORE_F64: return launch_batch2<LBM_STORE_F64>(a);
@@ -535,6 +671,12 @@ hipError_t batch_launch_steps(lbm_batch *b, int steps, const long long *ctr, lon
 // Steps per launch of a batch: two unless the caller has asked for single
 // steps.
 int batch_fuse(const lbm_batch *b) { return b->fuse_max; }
+
+// Steps per launch while enough steps are left (the table has been uploaded).
+int batch_steps(const lbm_batch *b)
+{
+    return b->total_tilesd > 0 ? kDeepSteps : batch_fuse(b);
+}
 
 // Average duration in microseconds of `reps` calls of fn on `stream`, after
 // `warm` untimed calls.  Returns a negative value on a HIP error.
@@ -611,7 +753,7 @@ lbm_status batch_upload(lbm_batch *b)
     b->t_at_upload.clear();
     b->cur_at_upload.clear();
     b->nxt_at_upload.clear();
-    int tile0 = 0, tile0_2 = 0;
+    int tile0 = 0, tile0_2 = 0, tile0_d = 0;
     const int align = strip_align(b->storage), align2 = strip_align2(b->storage);
     const bool two = batch_fuse(b) == 2;
     if (two && b->auto_rows2 && !b->members.empty()) {
@@ -641,25 +783,44 @@ lbm_status batch_upload(lbm_batch *b)
             }
         }
     }
+    bool deep = two && b->deep && b->force_on && !b->members.empty();
+    if (deep) {
+        std::vector<int32_t> sizes;
+        for (const lbm_handle *h : b->members) {
+            sizes.push_back(h->p.nx);
+            sizes.push_back(h->p.ny);
+        }
+        deep = deep_shape(DeepSizes{&sizes[0], &sizes[1], (int)b->members.size(), 2}, b->storage,
+                          b->members[0]->cus, &b->bxd, &b->rowsd);
+    }
     for (lbm_handle *h : b->members) {
-        BatchEntry e;
-        e.c = h->c;
-        if (!make_tiles(h->p.nx, h->p.ny, b->bx, std::min(b->rows, h->p.ny), align, &e.tl,
+        Tiles tl, tl2{0, 0, 0, 0}, tld{0, 0, 0, 0};
+        if (!make_tiles(h->p.nx, h->p.ny, b->bx, std::min(b->rows, h->p.ny), align, &tl,
                         1ll << 30) ||
             (two && !make_tiles2(h->p.nx, h->p.ny, b->bx2, std::min(b->rows2, h->p.ny), align2,
-                                 &e.tl2))) {
+                                 &tl2))) {
             b->last_error = "launch shape does not fit a lattice of the batch";
             return LBM_ERR_INVALID_ARG;
         }
-        if (!two) e.tl2 = Tiles{0, 0, 0, 0};
+        if (deep && !make_tilesd(h->p.nx, h->p.ny, b->bxd, std::min(b->rowsd, h->p.ny), &tld)) {
+            b->last_error = "deep launch shape does not fit a lattice of the batch";
+            return LBM_ERR_INVALID_ARG;
+        }
+        BatchEntry e;
+        e.c = h->c;
+        e.tl = BatchTiles{tl.nstrips, tl.nseg, tl.width};
+        e.tl2 = BatchTiles{tl2.nstrips, tl2.nseg, tl2.width};
+        e.tld = BatchTiles{tld.nstrips, tld.nseg, tld.width};
         e.buf[0] = h->cur;
         e.buf[1] = h->nxt;
         e.err = h->err;
         e.t0 = h->t;
         e.tile0 = tile0;
         e.tile0_2 = tile0_2;
-        tile0 += e.tl.ntiles;
-        tile0_2 += e.tl2.ntiles;
+        e.tile0_d = tile0_d;
+        tile0 += tl.ntiles;
+        tile0_2 += tl2.ntiles;
+        tile0_d += tld.ntiles;
         b->h_table.push_back(e);
         b->t_at_upload.push_back(h->t);
         b->cur_at_upload.push_back(h->cur);
@@ -667,6 +828,7 @@ lbm_status batch_upload(lbm_batch *b)
     }
     b->total_tiles = tile0;
     b->total_tiles2 = tile0_2;
+    b->total_tilesd = tile0_d;
     hipError_t e = hipSuccess;
     if (!b->h_table.empty())
         e = hipMemcpyAsync(b->d_table, b->h_table.data(), b->h_table.size() * sizeof(BatchEntry),
@@ -707,7 +869,7 @@ bool batch_stale(const lbm_batch *b)
     return false;
 }
 
-// Capture kGraphSteps batched steps in a graph: launches of batch_fuse(b)
+// Capture kGraphSteps batched steps in a graph: launches of batch_steps(b)
 // steps at their offsets from the device counters, then one kernel that
 // moves the counters on by the whole graph.  An even number of launches, so
 // a replay leaves every lattice's state in the buffer it started from.
@@ -717,7 +879,7 @@ hipError_t batch_capture(lbm_batch *b)
     hipError_t e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
     hipError_t le = hipSuccess;
-    const int per = batch_fuse(b), n = kGraphSteps / per;
+    const int per = batch_steps(b), n = kGraphSteps / per;
     for (int k = 0; k < n && le == hipSuccess; ++k)
         le = batch_launch_steps(b, per, b->d_ctr, (long long)k * per, k);
     if (le == hipSuccess) {
@@ -825,6 +987,7 @@ lbm_status lbm_init(const lbm_params *params, void *d_workspace, size_t workspac
                             &h->seg_rows2, &h->tiles2)
                   ? 2
                   : 1;
+    h->deep = default_deep(*params, h->cus, &h->bxd, &h->seg_rowsd, &h->tilesd);
 
     const size_t n = (size_t)params->nx * params->ny;
     const unsigned blocks = (unsigned)((n + 255) / 256);
@@ -853,6 +1016,12 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps)
     }
     int64_t k = 0;
     if (h->fuse == 2) {
+        for (; h->deep && k + kDeepSteps <= nsteps; k += kDeepSteps) {
+            hipError_t e = run_deep(h, h->cur, h->nxt);
+            if (e != hipSuccess) return dev_fail(h, e, "launching the deep kernel");
+            std::swap(h->cur, h->nxt);
+            h->t += kDeepSteps;
+        }
         for (; k + 2 <= nsteps; k += 2) {
             hipError_t e = run_sweep2(h, h->cur, h->nxt);
             if (e != hipSuccess) return dev_fail(h, e, "launching the two-step kernel");
@@ -1005,6 +1174,9 @@ lbm_status lbm_set_fusion(lbm_handle *h, int32_t steps, int32_t block_x, int32_t
         return LBM_ERR_INVALID_ARG;
     }
     h->fuse = 2;
+    // a shape of the caller's is used for every pair of steps
+    h->deep = block_x == 0 && seg_rows == 0 &&
+              default_deep(h->p, h->cus, &h->bxd, &h->seg_rowsd, &h->tilesd);
     h->bx2 = bx;
     h->seg_rows2 = rows;
     h->tiles2 = tl;
@@ -1119,6 +1291,18 @@ lbm_status lbm_autotune(lbm_handle *h, double out[3])
         make_tiles2(h->p.nx, h->p.ny, bx2, rows2, strip_align2(h->p.storage), &h->tiles2);
         h->bx2 = bx2;
         h->seg_rows2 = rows2;
+        // the deep pass at its default shape
+        double bestd = 1e300;
+        if (default_deep(h->p, h->cus, &h->bxd, &h->seg_rowsd, &h->tilesd)) {
+            auto deep = [&] { return run_deep(h, h->cur, h->nxt); };
+            for (int k = 0; k < 3; ++k) {
+                const double us = time_launches(h->stream, 20, deep, 5);
+                if (us < 0) return dev_fail(h, hipGetLastError(), "timing a launch shape");
+                bestd = std::min(bestd, us / kDeepSteps);
+            }
+        }
+        h->deep = bestd < std::min(best1, best2);
+        if (h->deep) best2 = bestd;
         if (best1 < best2) h->fuse = 1;
     }
     if (out) {
@@ -1165,8 +1349,12 @@ lbm_status lbm_batch_create(int32_t capacity, void *d_workspace, size_t workspac
     b->bx2 = 256;
     b->rows2 = kBatchRows2;
     b->auto_rows2 = true;
+    b->deep = true;
+    b->bxd = 256;
+    b->rowsd = 0;
     b->total_tiles = 0;
     b->total_tiles2 = 0;
+    b->total_tilesd = 0;
     b->graph_valid = false;
     *out = b;
     return LBM_OK;
@@ -1219,7 +1407,7 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps)
         if (st != LBM_OK) return st;
     }
     int64_t done = 0, launches = 0;
-    const int per = batch_fuse(b);
+    const int per = batch_steps(b);
     // the legacy null stream cannot be captured: there every launch is made
     // on its own
     const bool graphs = b->stream != nullptr;
@@ -1250,7 +1438,7 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps)
         b->ctr_launches = l0 + kGraphSteps / per;
     }
     while (done < nsteps) {
-        const int k = nsteps - done >= per ? per : 1;
+        const int k = nsteps - done >= per ? per : (nsteps - done >= batch_fuse(b) ? batch_fuse(b) : 1);
         const hipError_t e =
             batch_launch_steps(b, k, nullptr, b->steps_since_upload + done,
                                (int)((b->launches_since_upload + launches) & 1));
@@ -1342,6 +1530,18 @@ lbm_status lbm_batch_autotune(lbm_batch *b, double out[3])
         }
         b->bx2 = bx2;
         b->rows2 = rows2;
+        // the deep pass at its default shape
+        b->deep = true;
+        double bestd = 1e300;
+        if (batch_upload(b) == LBM_OK && b->total_tilesd > 0) {
+            auto deep = [&] { return batch_launch_steps(b, kDeepSteps, nullptr, 0, 0); };
+            for (int k = 0; k < 3; ++k) {
+                const double us = time_launches(b->stream, 20, deep, 5);
+                if (us >= 0) bestd = std::min(bestd, us / kDeepSteps);
+            }
+        }
+        b->deep = bestd < std::min(best1, best2);
+        if (b->deep) best2 = bestd;
     }
     const bool two = try_two && best2 <= best1;
     b->fuse_max = two ? 2 : 1;
@@ -1380,6 +1580,7 @@ lbm_status lbm_batch_set_launch(lbm_batch *b, int32_t steps, int32_t block_x, in
             return LBM_ERR_INVALID_ARG;
         }
         b->bx2 = block_x;
+        b->deep = false;
         b->auto_rows2 = seg_rows == 0;
         if (seg_rows > 0) b->rows2 = seg_rows;
     } else if (steps == 1) {

@@ -7,7 +7,7 @@
 //                    batched single steps, initialisation and the
 //                    population permutation; 2: the two-step pass, alone
 //                    and batched.
-#include "lbm_kernels.hpp"
+#include "lbm_deep.hpp"
 
 #if !defined(LBM_INST_ST) || !defined(LBM_INST_FAMILY)
 #error "compile with -DLBM_INST_ST=<0..3> -DLBM_INST_FAMILY=<1|2>"
@@ -16,6 +16,8 @@
 namespace lbmk {
 #if LBM_INST_FAMILY == 1
 LBM_DECLARE_FAMILY1(, LBM_INST_ST)
+#elif LBM_INST_FAMILY == 3
+LBM_DECLARE_FAMILY3(, LBM_INST_ST)
 #else
 LBM_DECLARE_FAMILY2(, LBM_INST_ST)
 #endif

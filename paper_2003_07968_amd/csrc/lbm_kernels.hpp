@@ -106,6 +106,7 @@ inline bool is_f16(int storage)
 struct Coeffs {
     int nx, ny;
     int pitch;      // stride between rows y and y + 1 of one population, in elements
+    int r_pitch;    // per-cell mode: row pitch of the reference block, in floats
     size_t plane;   // stride between populations i and i + 1 of one row, in elements
     double omega;   // 1/tau
     double guo;     // 1 - 1/(2 tau), Eq. GFSBGK
@@ -121,12 +122,9 @@ struct Coeffs {
     double rho_ref; // populations are stored as f_i - w_i rho_ref (0 for FP64 and the
                     // per-cell mode)
     size_t r_off;   // per-cell mode: byte offset of the FP32 reference block in a buffer
-    int r_pitch;    // per-cell mode: row pitch of that block, in floats
     double s_e, s_z, s_q; // MRT rates 1/tau_e, 1/tau_zeta, 1/tau_q (the stress rows use omega)
-    int coll;       // lbm_collision
-    int force_on;
-    int trace_alt;
-    int storage;
+    int8_t coll;    // lbm_collision
+    int8_t force_on, trace_alt, storage;
 };
 
 // The coefficients in the arithmetic type of a storage mode.
@@ -142,7 +140,11 @@ struct Phys {
     R m2_0, m2_1, m2_2, m2_58, m2_xy; // cA/9 times the M2 weights of s0, -s24, s13, s58, s5-s6
     R t0, t1, t2;                     // (cSC + cB tr0)/9, cB tr1/9, cB tr2/9
     R keep, om3, g3;                  // 1 - omega, omega/3, guo/3
-    __device__ explicit Phys(const Coeffs &c)
+    R m3g, om2;                       // -3 guo, omega/2 (collide)
+    // collide_mrt: 1 - s and 1 - s/2 of each rate (n: omega, the stress rows)
+    R ke, he, kz, hz, kq, hq, kn, hn;
+    Phys() = default;
+    __host__ __device__ explicit Phys(const Coeffs &c)
         : omega((R)c.omega), guo((R)c.guo), eos_b((R)c.eos_b), kcT((R)c.kcT), ka((R)c.ka),
           invG((R)c.invG), cSC((R)c.cSC), cA((R)c.cA), cB((R)c.cB), rho_ref((R)c.rho_ref),
           s_e((R)c.s_e), s_z((R)c.s_z), s_q((R)c.s_q), g_kcT((R)(c.kcT * c.invG)),
@@ -153,7 +155,10 @@ struct Phys {
           t0((R)((c.cSC + c.cB * (c.trace_alt ? -10.0 / 27.0 : -8.0 / 27.0)) / 9.0)),
           t1((R)(c.cB * (c.trace_alt ? 2.0 / 27.0 : 1.0 / 27.0) / 9.0)),
           t2((R)(c.cB * (c.trace_alt ? 1.0 / 54.0 : 1.0 / 27.0) / 9.0)),
-          keep((R)(1.0 - c.omega)), om3((R)(c.omega / 3.0)), g3((R)(c.guo / 3.0))
+          keep((R)(1.0 - c.omega)), om3((R)(c.omega / 3.0)), g3((R)(c.guo / 3.0)),
+          m3g(R(-3) * guo), om2(R(0.5) * omega), ke(R(1) - s_e), he(R(1) - R(0.5) * s_e),
+          kz(R(1) - s_z), hz(R(1) - R(0.5) * s_z), kq(R(1) - s_q), hq(R(1) - R(0.5) * s_q),
+          kn(R(1) - omega), hn(R(1) - R(0.5) * omega)
     {
     }
 };
@@ -437,11 +442,11 @@ __device__ __forceinline__ void collide(R d[kQ], R ref, R rho, R ux, R uy, R Jx,
     const R om = P.omega, g = P.guo, keep = P.keep;
     const R usq = fma(ux, ux, uy * uy);
     const R uF = fma(ux, Fx, uy * Fy);
-    const R A = fma(om, fma(rho, R(-1.5) * usq, kNoRef<R> ? rho : rho - ref), R(-3) * g * uF);
+    const R A = fma(om, fma(rho, R(-1.5) * usq, kNoRef<R> ? rho : rho - ref), P.m3g * uF);
     d[0] = fma(keep, d[0], R(4.0 / 9.0) * A);
     // axis directions (w = 1/9): w h = omega rho/2, w m = g, w B = (omega J + g F)/3
     const R A1 = R(1.0 / 9.0) * A;
-    const R h1 = R(0.5) * om * rho;
+    const R h1 = P.om2 * rho;
     const R Bx = fma(P.om3, Jx, P.g3 * Fx), By = fma(P.om3, Jy, P.g3 * Fy);
     const R mx = g * Fx, my = g * Fy;
     const R Tx = fma(ux, fma(h1, ux, mx), A1);
@@ -494,16 +499,14 @@ __device__ __forceinline__ void collide_mrt(R d[kQ], R rho, R ux, R uy, R Fx, R 
     const R uF6 = R(6) * fma(ux, Fx, uy * Fy);
     const R rusq3 = R(3) * rho * usq;
     const R se = P.s_e, sz = P.s_z, sq = P.s_q, sn = P.omega;
-    const R es = fma(R(1) - se, e, fma(se, fma(R(-2), dr, rusq3), (R(1) - R(0.5) * se) * uF6));
-    const R zs = fma(R(1) - sz, z, fma(sz, dr - rusq3, -(R(1) - R(0.5) * sz) * uF6));
+    const R es = fma(P.ke, e, fma(se, fma(R(-2), dr, rusq3), P.he * uF6));
+    const R zs = fma(P.kz, z, fma(sz, dr - rusq3, -P.hz * uF6));
     const R jxs = jx + Fx, jys = jy + Fy;
-    const R gq = R(1) - R(0.5) * sq;
-    const R qxs = fma(R(1) - sq, qx, -fma(sq * rho, ux, gq * Fx));
-    const R qys = fma(R(1) - sq, qy, -fma(sq * rho, uy, gq * Fy));
-    const R gn = R(1) - R(0.5) * sn;
-    const R pxxs = fma(R(1) - sn, pxx,
-                       fma(sn * rho, fma(ux, ux, -uy * uy), gn * R(2) * fma(ux, Fx, -uy * Fy)));
-    const R pxys = fma(R(1) - sn, pxy, fma(sn * rho, ux * uy, gn * fma(ux, Fy, uy * Fx)));
+    const R qxs = fma(P.kq, qx, -fma(sq * rho, ux, P.hq * Fx));
+    const R qys = fma(P.kq, qy, -fma(sq * rho, uy, P.hq * Fy));
+    const R pxxs = fma(P.kn, pxx,
+                       fma(sn * rho, fma(ux, ux, -uy * uy), P.hn * R(2) * fma(ux, Fx, -uy * Fy)));
+    const R pxys = fma(P.kn, pxy, fma(sn * rho, ux * uy, P.hn * fma(ux, Fy, uy * Fx)));
 
     const R r9 = dr * R(1.0 / 9.0);
     const R A1 = fma(es, R(-1.0 / 36.0), fma(zs, R(-1.0 / 18.0), r9));
@@ -923,15 +926,23 @@ __global__ __launch_bounds__(BX, (kMinWaves<ST, COLL>)) void sweep_kernel(const 
                                               t, err, fo, rho_snap, partials);
 }
 
+// The tiles of one lattice of a batch (ntiles = nstrips nseg).
+struct BatchTiles {
+    int nstrips, nseg, width;
+};
+
 // One lattice of a batch, as the batched step kernel sees it.
 struct BatchEntry {
     Coeffs c;
-    Tiles tl, tl2;            // tiles of a single step and of the two-step pass
+    BatchTiles tl, tl2, tld;  // tiles of a single step, of the two-step and of the deep pass
     const void *buf[2];       // population buffers; the first batched launch reads buf[0]
     unsigned long long *err;  // the lattice's sticky error word
     long long t0;             // the lattice's step count before the batched steps
-    int tile0, tile0_2;       // its first tile in the single-step / two-step batch grid
+    int tile0, tile0_2, tile0_d;  // its first tile in each of the three batch grids
 };
+// The serving loop's batch tables are part of its arena: an entry that grows
+// takes memory from the jobs of a caller who sized it before.
+static_assert(sizeof(BatchEntry) <= 232, "batch table entries must not grow");
 
 // Lattice of batch tile b: the last entry whose first tile (member F) is <= b
 // (binary search over the table, uniform per workgroup).
@@ -974,13 +985,14 @@ struct BatchTile {
     long long t;
     int tile;
 };
-template <int BatchEntry::*F, Tiles BatchEntry::*TL>
+template <int BatchEntry::*F, BatchTiles BatchEntry::*TL>
 __device__ __forceinline__ BatchTile batch_tile(const BatchEntry *__restrict__ table, int nlat,
                                                 int b, long long steps, int parity)
 {
     const BatchEntry &e = batch_entry<F>(table, nlat, b);
+    const BatchTiles t = e.*TL;
     return BatchTile{e.c,
-                     e.*TL,
+                     Tiles{t.nstrips, t.nseg, t.nstrips * t.nseg, t.width},
                      as_global(e.buf[parity]),
                      as_global(const_cast<void *>(e.buf[parity ^ 1])),
                      as_global(e.err),
@@ -1764,6 +1776,14 @@ hipError_t launch_permute(const void *in, void *out, const Coeffs &c, int to_can
 #define LBM_DECLARE_FAMILY2(EXT, ST)                                                          \
     EXT template hipError_t launch_sweep2<ST>(const SweepArgs &);                             \
     EXT template hipError_t launch_batch2<ST>(const BatchArgs &);
+// Launchers of the deep pass (lbm_deep.hpp): kDeepSteps steps of one lattice
+// or of a batch in one launch, with the force.
+constexpr int kDeepSteps = 4;
+template <int ST> hipError_t launch_deep(const SweepArgs &a);
+template <int ST> hipError_t launch_batch_deep(const BatchArgs &a);
+#define LBM_DECLARE_FAMILY3(EXT, ST)                                                          \
+    EXT template hipError_t launch_deep<ST>(const SweepArgs &);                               \
+    EXT template hipError_t launch_batch_deep<ST>(const BatchArgs &);
 #define LBM_EXTERN extern
 LBM_DECLARE_FAMILY1(LBM_EXTERN, LBM_STORE_F64)
 LBM_DECLARE_FAMILY1(LBM_EXTERN, LBM_STORE_F32_SHIFTED)
@@ -1773,6 +1793,10 @@ LBM_DECLARE_FAMILY2(LBM_EXTERN, LBM_STORE_F64)
 LBM_DECLARE_FAMILY2(LBM_EXTERN, LBM_STORE_F32_SHIFTED)
 LBM_DECLARE_FAMILY2(LBM_EXTERN, LBM_STORE_F16_SHIFTED)
 LBM_DECLARE_FAMILY2(LBM_EXTERN, LBM_STORE_F16_LOCAL)
+LBM_DECLARE_FAMILY3(LBM_EXTERN, LBM_STORE_F64)
+LBM_DECLARE_FAMILY3(LBM_EXTERN, LBM_STORE_F32_SHIFTED)
+LBM_DECLARE_FAMILY3(LBM_EXTERN, LBM_STORE_F16_SHIFTED)
+LBM_DECLARE_FAMILY3(LBM_EXTERN, LBM_STORE_F16_LOCAL)
 #undef LBM_EXTERN
 
 
