@@ -108,20 +108,23 @@ __device__ __forceinline__ bool unroll_while(F &&f, std::integer_sequence<int, J
 // being formed once in registers of its own.
 __device__ __forceinline__ void opaque(uint32_t &v) { asm("" : "+v"(v)); }
 
-// Coefficients formed by vector instructions, moved to scalar registers (the
-// compiler, which knows them to be uniform, drops its own readfirstlane and
-// keeps them in vector registers of every wave).
+// Coefficients formed by vector instructions, moved to scalar registers.  The
+// empty asm statement makes the value look divergent: a readfirstlane of a
+// value known to be uniform is dropped, and the value stays in vector
+// registers of every wave.
 template <class V>
 __device__ __forceinline__ V in_scalar_registers(const V &v)
 {
     static_assert(sizeof(V) % 4 == 0);
     struct Words {
-        uint32_t w[sizeof(V) / 4];
+        int w[sizeof(V) / 4];
     };
     Words a = __builtin_bit_cast(Words, v);
 #pragma unroll
-    for (uint32_t &w : a.w)
-        asm("v_readfirstlane_b32 %0, %1" : "=s"(w) : "v"(w));
+    for (int &w : a.w) {
+        asm("" : "+v"(w));
+        w = __builtin_amdgcn_readfirstlane(w);
+    }
     return __builtin_bit_cast(V, a);
 }
 
