@@ -64,6 +64,14 @@ __global__ void copy_plane(const double *__restrict__ a, double *__restrict__ b,
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// A launch of kDeepSteps steps: the deep pass (bx columns per step, segments of
+// `rows` rows) or the block pass (regions of bx rows), and its predicted time.
+struct FourShape {
+    bool block;
+    int bx, rows;
+    double us;
+};
+
 }  // namespace
 
 struct lbm_handle {
@@ -82,9 +90,9 @@ struct lbm_handle {
     int cus;                 // compute units of the device (default shapes)
     int bx2, seg_rows2;      // launch shape of the two-step pass
     Tiles tiles2;
-    bool deep;               // the deep pass is used for whole groups of kDeepSteps steps
-    int bxd, seg_rowsd;      // its launch shape
-    Tiles tilesd;
+    bool four;               // whole groups of kDeepSteps steps are taken in one launch
+    FourShape shape4;        // its form and shape
+    Tiles tiles4;
     int device;              // HIP device current at lbm_init
     lbm_status sticky;
     std::string last_error;
@@ -144,9 +152,9 @@ struct lbm_batch {
     int bx, rows;             // single-step shape
     int bx2, rows2;           // two-step shape
     bool auto_rows2;          // rows2 chosen at each upload (until autotuned)
-    bool deep;                // the deep pass may be used (no shape was asked for)
-    int bxd, rowsd;           // its shape, chosen at each upload
-    int total_tiles, total_tiles2, total_tilesd;  // total_tilesd 0: not used
+    bool four;                // launches of kDeepSteps steps may be used (no shape was asked for)
+    FourShape shape4;         // their form and shape, chosen at each upload
+    int total_tiles, total_tiles2, total_tiles4;  // total_tiles4 0: not used
     hipGraphExec_t graph;     // kGraphSteps batched steps, valid with the table
     bool graph_valid;
     std::string last_error;
@@ -154,7 +162,6 @@ struct lbm_batch {
 
 namespace {
 
-constexpr int kHaloD = 2 * kDeepSteps - 1;
 constexpr int kGraphSteps = 8;    // even: a multiple of the steps per launch
 constexpr int kBatchRows2 = 24;   // segment rows of the two-step pass in a batch
 const int kBatchRowsCand2[] = {2, 3, 4, 6, 8, 12, 16, 20, 24, 32, 40};
@@ -392,40 +399,60 @@ bool default_rows2(int nx, int ny, int storage, int bx, int cus, int *rows, Tile
     }
 }
 
-// Tiles of the deep pass: kHaloD halo columns on each side of a strip, strips
-// of a multiple of 16 columns as in the two-step pass.
+// Strip width of the deep pass: kHaloD halo columns on each side, strips of a
+// multiple of 16 columns as in the two-step pass.
 int deep_width(int nx, int bx)
 {
     const int w = bx - 2 * kHaloD;
     return nx > w ? w / 16 * 16 : nx;
 }
 
-bool make_tilesd(int nx, int ny, int bx, int seg_rows, Tiles *tl)
+bool make_tiles4(int nx, int ny, const FourShape &f, Tiles *tl)
 {
-    const int w = deep_width(nx, bx);
-    tl->width = w;
-    tl->nstrips = (nx + w - 1) / w;
-    tl->nseg = (ny + seg_rows - 1) / seg_rows;
+    if (f.block) {
+        tl->width = kBlockCols;
+        tl->nstrips = (nx + kBlockCols - 1) / kBlockCols;
+        const int rows = f.bx - 2 * kHaloD;
+        tl->nseg = (ny + rows - 1) / rows;
+    } else {
+        tl->width = deep_width(nx, f.bx);
+        tl->nstrips = (nx + tl->width - 1) / tl->width;
+        const int rows = std::min(f.rows, ny);
+        tl->nseg = (ny + rows - 1) / rows;
+    }
     const long long nt = (long long)tl->nstrips * tl->nseg;
     if (nt > kMaxTiles) return false;
     tl->ntiles = (int)nt;
     return true;
 }
 
-// Launch shape of the deep pass for a set of lattices (one, or a batch's
-// members): the columns per step (64, 128 or 256) and the segment length that
-// minimise
-//     rounds x (rows + kDeepFill) x t(lanes in use per CU).
-// A CU runs kDeepSteps x 256 threads at once (twice that with FP32 and FP16
-// storage, whose kernels fit 64 registers), or as many in narrower
-// workgroups; an iteration of a CU that is filled to the fraction u takes
-// t = max(0.4, 0.16 + 0.84 u) of a full one (2048^2-type lattices: FP32 0.95
-// us with one workgroup per CU, 1.63 us with two; a lone narrow workgroup is
-// bound by latency).  kDeepFill: a walk takes 21 iterations more than its
-// rows, in which part of the steps are idle.
-constexpr int kDeepFill = 16;
+// Predicted times, in us per launch (measured on square lattices of 16 to 8192
+// and 2048 x 8192 cells, BGK; the MRT collision takes 1.1 to 1.2 times as
+// long in either form).
+//
+// Deep pass: a CU runs kDeepSteps x 256 threads at once (twice that with FP32
+// and FP16 storage, whose kernels fit 64 registers), or as many in narrower
+// workgroups.  An iteration of a CU filled to the fraction u takes
+// max(0.4, 0.16 + 0.84 u) of a full one's kIterUs (FP32: 0.95 us with one
+// workgroup of 256 columns per CU, 1.63 with two; a lone narrow workgroup is
+// bound by latency).  A walk of r rows costs r + 9 of them (the mean rows of
+// its four steps) and 6 us of iterations in which most steps are idle, a
+// launch 3 us.
+constexpr double kLaunchUs = 3.0, kFillUs = 6.0, kFillRows = 9.0;
+const double kIterUs[] = {1.63, 1.63, 1.55, 1.20};  // by storage mode
 const int kDeepRowsCand[] = {2,  3,  4,  5,  6,  8,  10, 12,  14,  16,  20,  24,  28,  32,  37,  42,
                              48, 56, 64, 74, 84, 96, 110, 128, 147, 170, 196, 220, 256, 293, 341, 400};
+// Block pass: workgroups per CU and the time of one workgroup alone and of a
+// full CU, by rows of the region.
+struct BlockTime {
+    int rows, per_cu;
+    double one, full;
+};
+const BlockTime kBlockTimes[3][4] = {
+    {{16, 3, 4.6, 7.2}, {20, 2, 5.2, 10.6}, {24, 2, 6.6, 10.5}, {32, 1, 7.9, 7.9}},    // FP64
+    {{16, 4, 3.8, 6.0}, {20, 3, 3.9, 7.6}, {24, 2, 4.4, 6.6}, {32, 2, 5.7, 8.5}},      // FP32, FP16
+    {{16, 4, 4.5, 7.3}, {20, 3, 4.8, 10.0}, {24, 2, 6.0, 8.5}, {32, 2, 7.1, 10.7}}};   // per-cell
+constexpr double kBlockLaunchUs = 2.0;
 
 int deep_wgs_per_cu(int storage, int bx)
 {
@@ -433,33 +460,30 @@ int deep_wgs_per_cu(int storage, int bx)
     return (two ? 2 : 1) * 256 / bx;
 }
 
-// Sizes and strip counts of the lattices a shape is chosen for.
-struct DeepSizes {
+// Sizes of the lattices a shape is chosen for: lattice k is nx[k stride] by
+// ny[k stride].
+struct LatticeSizes {
     const int32_t *nx, *ny;
-    int count, stride;  // the sizes of lattice k are at nx[k stride], ny[k stride]
+    int count, stride;
 };
 
-// Cost of one launch in units of a full CU's iteration; strips[k] strips in
-// lattice k.  Negative if a lattice needs too many tiles.
-double deep_cost(const DeepSizes &z, const int *strips, int storage, int cus, int bx, int rows)
+// The faster form and shape for one lattice or a batch's members by these
+// times.  Where the two come out within 15% the deep pass is taken, whose
+// prediction is the higher one on small lattices (512^2 FP64: deep 35
+// predicted, 26 measured; block 33.5 and 29).  So one square lattice goes
+// to the block pass up to about 200k cells in FP64 and 450k otherwise
+// (measured, us per step, deep / block: FP64 64^2 4.0 / 1.7, 200^2 4.5 / 2.1,
+// 517 x 301 6.1 / 4.5, 512^2 6.5 / 7.3; FP32 64^2 3.9 / 1.5, 512^2 5.6 / 4.7,
+// 700^2 6.8 / 6.7, 1024^2 8.9 / 13.4).
+bool four_shape(const LatticeSizes &z, int storage, int cus, FourShape *out)
 {
-    long long tiles = 0;
-    for (int k = 0; k < z.count; ++k) {
-        const unsigned ny = (unsigned)z.ny[(size_t)k * z.stride], r = std::min((unsigned)rows, ny);
-        const long long t = (long long)strips[k] * ((ny + r - 1) / r);
-        if (t > kMaxTiles) return -1.0;
-        tiles += t;
-    }
-    const int per_cu = deep_wgs_per_cu(storage, bx);
-    const long long slots = (long long)per_cu * cus, full = tiles / slots, rest = tiles % slots;
-    const double u = (double)((rest + cus - 1) / cus) / per_cu;
-    const double last = rest ? std::max(0.4, 0.16 + 0.84 * u) : 0.0;
-    return ((double)full + last) * (rows + kDeepFill);
-}
-
-bool deep_shape(const DeepSizes &z, int storage, int cus, int *bx, int *rows)
-{
-    double best = -1.0;
+    out->us = -1.0;
+    // full rounds of workgroups, and what is left as a partial one
+    auto rounds = [&](long long tiles, int per_cu, double *u) {
+        const long long slots = (long long)per_cu * cus, rest = tiles % slots;
+        *u = (double)((rest + cus - 1) / cus) / per_cu;
+        return (double)(tiles / slots);
+    };
     std::vector<int> many((size_t)(z.count > 1 ? z.count : 0));
     int one, *strips = z.count > 1 ? many.data() : &one;
     for (int b : {256, 128, 64}) {
@@ -469,32 +493,56 @@ bool deep_shape(const DeepSizes &z, int storage, int cus, int *bx, int *rows)
             strips[k] = (nx + w - 1) / w;
             total += strips[k];
         }
+        const int per_cu = deep_wgs_per_cu(storage, b);
         auto consider = [&](int r) {
-            const double cost = deep_cost(z, strips, storage, cus, b, r);
-            if (cost >= 0.0 && (best < 0.0 || cost < best)) {
-                best = cost;
-                *bx = b;
-                *rows = r;
+            long long tiles = 0;
+            for (int k = 0; k < z.count; ++k) {
+                const unsigned ny = (unsigned)z.ny[(size_t)k * z.stride];
+                const unsigned rows = std::min((unsigned)r, ny);
+                const long long t = (long long)strips[k] * ((ny + rows - 1) / rows);
+                if (t > kMaxTiles) return;
+                tiles += t;
             }
+            double u;
+            const double full = rounds(tiles, per_cu, &u), walk = kIterUs[storage] * (r + kFillRows);
+            double us = kLaunchUs + full * (walk + kFillUs);
+            if (u > 0.0) us += walk * std::max(0.4, 0.16 + 0.84 * u) + kFillUs;
+            if (out->us < 0.0 || us < out->us) *out = FourShape{false, b, r, us};
         };
         for (int r : kDeepRowsCand)
             consider(r);
         // lengths that cut lattices of the first one's size into whole rounds
         for (int half = 1; half <= 8; ++half) {
-            const int slots = deep_wgs_per_cu(storage, b) * cus;
-            const int nseg = std::max(1, half * slots / 2 / total), ny = z.ny[0];
+            const int nseg = std::max(1, half * per_cu * cus / 2 / total), ny = z.ny[0];
             consider(std::max(2, (ny + nseg - 1) / nseg));
         }
     }
-    return best >= 0.0;
+    const bool deep_fits = out->us >= 0.0;
+    const double deep_us = out->us;
+    for (const BlockTime &t : kBlockTimes[storage == LBM_STORE_F64 ? 0 : (storage == LBM_STORE_F16_LOCAL ? 2 : 1)]) {
+        long long tiles = 0;
+        bool fits = true;
+        for (int k = 0; k < z.count && fits; ++k) {
+            Tiles tl;
+            fits = make_tiles4(z.nx[(size_t)k * z.stride], z.ny[(size_t)k * z.stride],
+                               FourShape{true, t.rows, 0, 0.0}, &tl);
+            tiles += tl.ntiles;
+        }
+        if (!fits) continue;
+        double u;
+        double us = kBlockLaunchUs + rounds(tiles, t.per_cu, &u) * t.full;
+        if (u > 0.0)
+            us += t.one + (t.per_cu > 1 ? (t.full - t.one) * (u * t.per_cu - 1.0) / (t.per_cu - 1) : 0.0);
+        if ((!deep_fits || 1.15 * us < deep_us) && (out->us < 0.0 || !out->block || us < out->us))
+            *out = FourShape{true, t.rows, 0, us};
+    }
+    return out->us >= 0.0;
 }
 
-bool default_deep(const lbm_params &p, int cus, int *bx, int *rows, Tiles *tl)
+bool default_four(const lbm_params &p, int cus, FourShape *f, Tiles *tl)
 {
-    if (!p.force_on) return false;
-    if (!deep_shape(DeepSizes{&p.nx, &p.ny, 1, 0}, p.storage, cus, bx, rows)) return false;
-    *rows = std::min(*rows, (int)p.ny);
-    return make_tilesd(p.nx, p.ny, *bx, *rows, tl);
+    return p.force_on && four_shape(LatticeSizes{&p.nx, &p.ny, 1, 0}, p.storage, cus, f) &&
+           make_tiles4(p.nx, p.ny, *f, tl);
 }
 
 // Compute units of the current device (256 on MI355X if the query fails).
@@ -554,16 +602,21 @@ hipError_t run_sweep2(lbm_handle *h, const void *src, void *dst)
 }
 
 // kDeepSteps time steps in one pass.
-hipError_t run_deep(lbm_handle *h, const void *src, void *dst)
+hipError_t run_four(lbm_handle *h, const void *src, void *dst)
 {
     SweepArgs a = sweep_args(h, src, dst, Fields{}, true);
-    a.tl = h->tilesd;
-    a.bx = h->bxd;
+    a.tl = h->tiles4;
+    a.bx = h->shape4.bx;
+    const bool block = h->shape4.block;
     switch (h->c.storage) {
-    case LBM_STORE_F64: return launch_deep<LBM_STORE_F64>(a);
-    case LBM_STORE_F32_SHIFTED: return launch_deep<LBM_STORE_F32_SHIFTED>(a);
-    case LBM_STORE_F16_SHIFTED: return launch_deep<LBM_STORE_F16_SHIFTED>(a);
-    case LBM_STORE_F16_LOCAL: return launch_deep<LBM_STORE_F16_LOCAL>(a);
+    case LBM_STORE_F64:
+        return block ? launch_block<LBM_STORE_F64>(a) : launch_deep<LBM_STORE_F64>(a);
+    case LBM_STORE_F32_SHIFTED:
+        return block ? launch_block<LBM_STORE_F32_SHIFTED>(a) : launch_deep<LBM_STORE_F32_SHIFTED>(a);
+    case LBM_STORE_F16_SHIFTED:
+        return block ? launch_block<LBM_STORE_F16_SHIFTED>(a) : launch_deep<LBM_STORE_F16_SHIFTED>(a);
+    case LBM_STORE_F16_LOCAL:
+        return block ? launch_block<LBM_STORE_F16_LOCAL>(a) : launch_deep<LBM_STORE_F16_LOCAL>(a);
     }
     return hipErrorInvalidValue;
 }
@@ -621,14 +674,14 @@ lbm_status read_sticky(lbm_handle *h)
 BatchArgs batch_args(const lbm_batch *b, int steps, const long long *ctr, long long steps_add,
                      int launches_add)
 {
-    const bool two = steps == 2, deep = steps == kDeepSteps;
+    const bool two = steps == 2, four = steps == kDeepSteps;
     return BatchArgs{b->d_table,
                      (int)b->members.size(),
                      ctr,
                      steps_add,
                      launches_add,
-                     deep ? b->bxd : (two ? b->bx2 : b->bx),
-                     (unsigned)(deep ? b->total_tilesd : (two ? b->total_tiles2 : b->total_tiles)),
+                     four ? b->shape4.bx : (two ? b->bx2 : b->bx),
+                     (unsigned)(four ? b->total_tiles4 : (two ? b->total_tiles2 : b->total_tiles)),
                      b->force_on,
                      b->coll,
                      b->stream};
@@ -642,11 +695,19 @@ hipError_t batch_launch_steps(lbm_batch *b, int steps, const long long *ctr, lon
 {
     const BatchArgs a = batch_args(b, steps, ctr, steps_add, launches_add);
     if (steps == kDeepSteps) {
+        const bool block = b->shape4.block;
         switch (b->storage) {
-        case LBM_STORE_F64: return launch_batch_deep<LBM_STORE_F64>(a);
-        case LBM_STORE_F32_SHIFTED: return launch_batch_deep<LBM_STORE_F32_SHIFTED>(a);
-        case LBM_STORE_F16_SHIFTED: return launch_batch_deep<LBM_STORE_F16_SHIFTED>(a);
-        case LBM_STORE_F16_LOCAL: return launch_batch_deep<LBM_STORE_F16_LOCAL>(a);
+        case LBM_STORE_F64:
+            return block ? launch_batch_block<LBM_STORE_F64>(a) : launch_batch_deep<LBM_STORE_F64>(a);
+        case LBM_STORE_F32_SHIFTED:
+            return block ? launch_batch_block<LBM_STORE_F32_SHIFTED>(a)
+                         : launch_batch_deep<LBM_STORE_F32_SHIFTED>(a);
+        case LBM_STORE_F16_SHIFTED:
+            return block ? launch_batch_block<LBM_STORE_F16_SHIFTED>(a)
+                         : launch_batch_deep<LBM_STORE_F16_SHIFTED>(a);
+        case LBM_STORE_F16_LOCAL:
+            return block ? launch_batch_block<LBM_STORE_F16_LOCAL>(a)
+                         : launch_batch_deep<LBM_STORE_F16_LOCAL>(a);
         }
         return hipErrorInvalidValue;
     }
@@ -675,7 +736,7 @@ int batch_fuse(const lbm_batch *b) { return b->fuse_max; }
 // Steps per launch while enough steps are left (the table has been uploaded).
 int batch_steps(const lbm_batch *b)
 {
-    return b->total_tilesd > 0 ? kDeepSteps : batch_fuse(b);
+    return b->total_tiles4 > 0 ? kDeepSteps : batch_fuse(b);
 }
 
 // Average duration in microseconds of `reps` calls of fn on `stream`, after
@@ -753,7 +814,7 @@ lbm_status batch_upload(lbm_batch *b)
     b->t_at_upload.clear();
     b->cur_at_upload.clear();
     b->nxt_at_upload.clear();
-    int tile0 = 0, tile0_2 = 0, tile0_d = 0;
+    int tile0 = 0, tile0_2 = 0, tile0_4 = 0;
     const int align = strip_align(b->storage), align2 = strip_align2(b->storage);
     const bool two = batch_fuse(b) == 2;
     if (two && b->auto_rows2 && !b->members.empty()) {
@@ -783,18 +844,18 @@ lbm_status batch_upload(lbm_batch *b)
             }
         }
     }
-    bool deep = two && b->deep && b->force_on && !b->members.empty();
-    if (deep) {
+    bool four = two && b->four && b->force_on && !b->members.empty();
+    if (four) {
         std::vector<int32_t> sizes;
         for (const lbm_handle *h : b->members) {
             sizes.push_back(h->p.nx);
             sizes.push_back(h->p.ny);
         }
-        deep = deep_shape(DeepSizes{&sizes[0], &sizes[1], (int)b->members.size(), 2}, b->storage,
-                          b->members[0]->cus, &b->bxd, &b->rowsd);
+        four = four_shape(LatticeSizes{&sizes[0], &sizes[1], (int)b->members.size(), 2}, b->storage,
+                          b->members[0]->cus, &b->shape4);
     }
     for (lbm_handle *h : b->members) {
-        Tiles tl, tl2{0, 0, 0, 0}, tld{0, 0, 0, 0};
+        Tiles tl, tl2{0, 0, 0, 0}, tl4{0, 0, 0, 0};
         if (!make_tiles(h->p.nx, h->p.ny, b->bx, std::min(b->rows, h->p.ny), align, &tl,
                         1ll << 30) ||
             (two && !make_tiles2(h->p.nx, h->p.ny, b->bx2, std::min(b->rows2, h->p.ny), align2,
@@ -802,25 +863,25 @@ lbm_status batch_upload(lbm_batch *b)
             b->last_error = "launch shape does not fit a lattice of the batch";
             return LBM_ERR_INVALID_ARG;
         }
-        if (deep && !make_tilesd(h->p.nx, h->p.ny, b->bxd, std::min(b->rowsd, h->p.ny), &tld)) {
-            b->last_error = "deep launch shape does not fit a lattice of the batch";
+        if (four && !make_tiles4(h->p.nx, h->p.ny, b->shape4, &tl4)) {
+            b->last_error = "four-step launch shape does not fit a lattice of the batch";
             return LBM_ERR_INVALID_ARG;
         }
         BatchEntry e;
         e.c = h->c;
         e.tl = BatchTiles{tl.nstrips, tl.nseg, tl.width};
         e.tl2 = BatchTiles{tl2.nstrips, tl2.nseg, tl2.width};
-        e.tld = BatchTiles{tld.nstrips, tld.nseg, tld.width};
+        e.tl4 = BatchTiles{tl4.nstrips, tl4.nseg, tl4.width};
         e.buf[0] = h->cur;
         e.buf[1] = h->nxt;
         e.err = h->err;
         e.t0 = h->t;
         e.tile0 = tile0;
         e.tile0_2 = tile0_2;
-        e.tile0_d = tile0_d;
+        e.tile0_4 = tile0_4;
         tile0 += tl.ntiles;
         tile0_2 += tl2.ntiles;
-        tile0_d += tld.ntiles;
+        tile0_4 += tl4.ntiles;
         b->h_table.push_back(e);
         b->t_at_upload.push_back(h->t);
         b->cur_at_upload.push_back(h->cur);
@@ -828,7 +889,7 @@ lbm_status batch_upload(lbm_batch *b)
     }
     b->total_tiles = tile0;
     b->total_tiles2 = tile0_2;
-    b->total_tilesd = tile0_d;
+    b->total_tiles4 = tile0_4;
     hipError_t e = hipSuccess;
     if (!b->h_table.empty())
         e = hipMemcpyAsync(b->d_table, b->h_table.data(), b->h_table.size() * sizeof(BatchEntry),
@@ -987,7 +1048,7 @@ lbm_status lbm_init(const lbm_params *params, void *d_workspace, size_t workspac
                             &h->seg_rows2, &h->tiles2)
                   ? 2
                   : 1;
-    h->deep = default_deep(*params, h->cus, &h->bxd, &h->seg_rowsd, &h->tilesd);
+    h->four = default_four(*params, h->cus, &h->shape4, &h->tiles4);
 
     const size_t n = (size_t)params->nx * params->ny;
     const unsigned blocks = (unsigned)((n + 255) / 256);
@@ -1016,9 +1077,9 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps)
     }
     int64_t k = 0;
     if (h->fuse == 2) {
-        for (; h->deep && k + kDeepSteps <= nsteps; k += kDeepSteps) {
-            hipError_t e = run_deep(h, h->cur, h->nxt);
-            if (e != hipSuccess) return dev_fail(h, e, "launching the deep kernel");
+        for (; h->four && k + kDeepSteps <= nsteps; k += kDeepSteps) {
+            hipError_t e = run_four(h, h->cur, h->nxt);
+            if (e != hipSuccess) return dev_fail(h, e, "launching the four-step kernel");
             std::swap(h->cur, h->nxt);
             h->t += kDeepSteps;
         }
@@ -1175,8 +1236,8 @@ lbm_status lbm_set_fusion(lbm_handle *h, int32_t steps, int32_t block_x, int32_t
     }
     h->fuse = 2;
     // a shape of the caller's is used for every pair of steps
-    h->deep = block_x == 0 && seg_rows == 0 &&
-              default_deep(h->p, h->cus, &h->bxd, &h->seg_rowsd, &h->tilesd);
+    h->four = block_x == 0 && seg_rows == 0 &&
+              default_four(h->p, h->cus, &h->shape4, &h->tiles4);
     h->bx2 = bx;
     h->seg_rows2 = rows;
     h->tiles2 = tl;
@@ -1291,18 +1352,18 @@ lbm_status lbm_autotune(lbm_handle *h, double out[3])
         make_tiles2(h->p.nx, h->p.ny, bx2, rows2, strip_align2(h->p.storage), &h->tiles2);
         h->bx2 = bx2;
         h->seg_rows2 = rows2;
-        // the deep pass at its default shape
-        double bestd = 1e300;
-        if (default_deep(h->p, h->cus, &h->bxd, &h->seg_rowsd, &h->tilesd)) {
-            auto deep = [&] { return run_deep(h, h->cur, h->nxt); };
+        // four steps per launch in the default shape
+        double best4 = 1e300;
+        if (default_four(h->p, h->cus, &h->shape4, &h->tiles4)) {
+            auto four = [&] { return run_four(h, h->cur, h->nxt); };
             for (int k = 0; k < 3; ++k) {
-                const double us = time_launches(h->stream, 20, deep, 5);
+                const double us = time_launches(h->stream, 20, four, 5);
                 if (us < 0) return dev_fail(h, hipGetLastError(), "timing a launch shape");
-                bestd = std::min(bestd, us / kDeepSteps);
+                best4 = std::min(best4, us / kDeepSteps);
             }
         }
-        h->deep = bestd < std::min(best1, best2);
-        if (h->deep) best2 = bestd;
+        h->four = best4 < std::min(best1, best2);
+        if (h->four) best2 = best4;
         if (best1 < best2) h->fuse = 1;
     }
     if (out) {
@@ -1349,12 +1410,11 @@ lbm_status lbm_batch_create(int32_t capacity, void *d_workspace, size_t workspac
     b->bx2 = 256;
     b->rows2 = kBatchRows2;
     b->auto_rows2 = true;
-    b->deep = true;
-    b->bxd = 256;
-    b->rowsd = 0;
+    b->four = true;
+    b->shape4 = FourShape{false, 256, 0, 0.0};
     b->total_tiles = 0;
     b->total_tiles2 = 0;
-    b->total_tilesd = 0;
+    b->total_tiles4 = 0;
     b->graph_valid = false;
     *out = b;
     return LBM_OK;
@@ -1530,18 +1590,18 @@ lbm_status lbm_batch_autotune(lbm_batch *b, double out[3])
         }
         b->bx2 = bx2;
         b->rows2 = rows2;
-        // the deep pass at its default shape
-        b->deep = true;
-        double bestd = 1e300;
-        if (batch_upload(b) == LBM_OK && b->total_tilesd > 0) {
-            auto deep = [&] { return batch_launch_steps(b, kDeepSteps, nullptr, 0, 0); };
+        // four steps per launch in the default shape
+        b->four = true;
+        double best4 = 1e300;
+        if (batch_upload(b) == LBM_OK && b->total_tiles4 > 0) {
+            auto four = [&] { return batch_launch_steps(b, kDeepSteps, nullptr, 0, 0); };
             for (int k = 0; k < 3; ++k) {
-                const double us = time_launches(b->stream, 20, deep, 5);
-                if (us >= 0) bestd = std::min(bestd, us / kDeepSteps);
+                const double us = time_launches(b->stream, 20, four, 5);
+                if (us >= 0) best4 = std::min(best4, us / kDeepSteps);
             }
         }
-        b->deep = bestd < std::min(best1, best2);
-        if (b->deep) best2 = bestd;
+        b->four = best4 < std::min(best1, best2);
+        if (b->four) best2 = best4;
     }
     const bool two = try_two && best2 <= best1;
     b->fuse_max = two ? 2 : 1;
@@ -1580,7 +1640,7 @@ lbm_status lbm_batch_set_launch(lbm_batch *b, int32_t steps, int32_t block_x, in
             return LBM_ERR_INVALID_ARG;
         }
         b->bx2 = block_x;
-        b->deep = false;
+        b->four = false;
         b->auto_rows2 = seg_rows == 0;
         if (seg_rows > 0) b->rows2 = seg_rows;
     } else if (steps == 1) {

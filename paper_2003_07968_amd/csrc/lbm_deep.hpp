@@ -495,7 +495,7 @@ __global__ __launch_bounds__(BX *T, (kDeepWaves<ST>)) void batch_deep_kernel(con
                                                            long long steps_add, int launches_add)
 {
     const BatchPos pos = batch_pos(d_ctr, steps_add, launches_add);
-    const BatchTile k = batch_tile<&BatchEntry::tile0_d, &BatchEntry::tld>(
+    const BatchTile k = batch_tile<&BatchEntry::tile0_4, &BatchEntry::tl4>(
         table, nlat, xcd_tile(blockIdx.x, gridDim.x), pos.steps, pos.parity);
     const auto P = in_scalar_registers(Phys<typename Store<ST>::R>(k.c));
     deep_tile<BX, T, ST, COLL>(k.src, k.dst, k.c, P, k.tl, k.tile, k.t, k.err);

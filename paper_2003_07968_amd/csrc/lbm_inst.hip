@@ -7,7 +7,7 @@
 //                    batched single steps, initialisation and the
 //                    population permutation; 2: the two-step pass, alone
 //                    and batched.
-#include "lbm_deep.hpp"
+#include "lbm_block.hpp"
 
 #if !defined(LBM_INST_ST) || !defined(LBM_INST_FAMILY)
 #error "compile with -DLBM_INST_ST=<0..3> -DLBM_INST_FAMILY=<1|2>"

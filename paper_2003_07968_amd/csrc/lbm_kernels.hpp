@@ -934,11 +934,11 @@ struct BatchTiles {
 // One lattice of a batch, as the batched step kernel sees it.
 struct BatchEntry {
     Coeffs c;
-    BatchTiles tl, tl2, tld;  // tiles of a single step, of the two-step and of the deep pass
+    BatchTiles tl, tl2, tl4;  // tiles of a single step, of the two-step pass and of four steps
     const void *buf[2];       // population buffers; the first batched launch reads buf[0]
     unsigned long long *err;  // the lattice's sticky error word
     long long t0;             // the lattice's step count before the batched steps
-    int tile0, tile0_2, tile0_d;  // its first tile in each of the three batch grids
+    int tile0, tile0_2, tile0_4;  // its first tile in each of the three batch grids
 };
 // The serving loop's batch tables are part of its arena: an entry that grows
 // takes memory from the jobs of a caller who sized it before.
@@ -1779,11 +1779,19 @@ hipError_t launch_permute(const void *in, void *out, const Coeffs &c, int to_can
 // Launchers of the deep pass (lbm_deep.hpp): kDeepSteps steps of one lattice
 // or of a batch in one launch, with the force.
 constexpr int kDeepSteps = 4;
+constexpr int kHaloD = 2 * kDeepSteps - 1;  // halo columns and rows of a tile
+// Block pass: columns of a workgroup's region and of the cells it advances.
+constexpr int kBlockW = 32, kBlockCols = kBlockW - 2 * kHaloD;
 template <int ST> hipError_t launch_deep(const SweepArgs &a);
 template <int ST> hipError_t launch_batch_deep(const BatchArgs &a);
+// Launchers of the block pass (lbm_block.hpp), likewise.
+template <int ST> hipError_t launch_block(const SweepArgs &a);
+template <int ST> hipError_t launch_batch_block(const BatchArgs &a);
 #define LBM_DECLARE_FAMILY3(EXT, ST)                                                          \
     EXT template hipError_t launch_deep<ST>(const SweepArgs &);                               \
-    EXT template hipError_t launch_batch_deep<ST>(const BatchArgs &);
+    EXT template hipError_t launch_batch_deep<ST>(const BatchArgs &);                         \
+    EXT template hipError_t launch_block<ST>(const SweepArgs &);                              \
+    EXT template hipError_t launch_batch_block<ST>(const BatchArgs &);
 #define LBM_EXTERN extern
 LBM_DECLARE_FAMILY1(LBM_EXTERN, LBM_STORE_F64)
 LBM_DECLARE_FAMILY1(LBM_EXTERN, LBM_STORE_F32_SHIFTED)

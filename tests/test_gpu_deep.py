@@ -19,9 +19,10 @@ from .helpers import oracle_params
 pytestmark = pytest.mark.gpu
 
 # tiny and wrapping; one and two strips of 64-, 128- and 256-column workgroups
-# (50, 114 and 242 columns fit one strip); several segments, odd row counts
+# (50, 114 and 242 columns fit one strip) and of 18-column blocks; several
+# segments, odd row counts
 SIZES = [(3, 3), (5, 19), (17, 9), (50, 33), (51, 16), (64, 64), (114, 7), (115, 40), (242, 31),
-         (243, 77), (200, 200), (301, 203), (1030, 517)]
+         (243, 77), (18, 18), (19, 37), (200, 200), (301, 203), (640, 640), (1030, 517)]
 
 
 def _case(nx, ny, storage, collision, seed=31, alt=False):
@@ -50,11 +51,14 @@ def test_default_steps_bitwise_equal_single_steps(storage, collision):
 
 @pytest.mark.parametrize("collision", ["bgk", "mrt"])
 @pytest.mark.parametrize("storage", ["f64", "f32", "f16", "f16l"])
-def test_default_batch_bitwise_equal_single_steps(storage, collision):
+@pytest.mark.parametrize("sizes", [SIZES, SIZES[:-2], [(24, 20)], [(1500, 700), (3, 3)]],
+                         ids=["all", "small", "one", "large"])
+def test_default_batch_bitwise_equal_single_steps(storage, collision, sizes):
+    # sets of lattices that the library advances in either form of long pass
     require_gpu()
     with torch.cuda.stream(torch.cuda.Stream()):
         cases = [_case(nx, ny, storage, collision, seed=70 + k)
-                 for k, (nx, ny) in enumerate(SIZES)]
+                 for k, (nx, ny) in enumerate(sizes)]
         solo = [gpu_lattice(p, r, launch=(256, 8)) for p, r in cases]
         mates = [gpu_lattice(p, r) for p, r in cases]
         batch = lbm.Batch(len(cases))
@@ -63,7 +67,7 @@ def test_default_batch_bitwise_equal_single_steps(storage, collision):
         for n in (7, 16, 3, 24, 4):
             batch.step(n)
             _ = torch.zeros(4, device="cuda").sum().item()  # unrelated work between replays
-            for s, m, size in zip(solo, mates, SIZES):
+            for s, m, size in zip(solo, mates, sizes):
                 s.step(n)
                 assert m.t == s.t
                 assert torch.equal(s.populations(), m.populations()), (size, n)
