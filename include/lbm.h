@@ -232,8 +232,9 @@ lbm_status lbm_set_launch(lbm_handle *h, int32_t block_x, int32_t seg_rows);
  * library's choice (256 threads; segments of 2..40 rows, as many as fill whole
  * rounds of the workgroups the device runs at once).  lbm_init selects 2.
  * With 2 and neither block_x nor seg_rows given, lbm_step may take more than
- * two steps per launch while enough steps are left (four in the deep pass);
- * pairs and an odd remainder follow in the forms above.  The results and the
+ * two steps per launch (four, in the deep pass or, on small lattices, the
+ * block pass, which takes one to three at the end of a call as well); pairs
+ * and an odd remainder follow in the forms above.  The results and the
  * first domain error are the same, bitwise.  A shape given here is used for
  * every pair of steps.
  * Batches have their own setting (lbm_batch_set_fusion). */
@@ -268,9 +269,10 @@ lbm_status lbm_autotune(lbm_handle *h, double out[3]);
  * steps (the two-step pass; one per step after lbm_batch_set_fusion(b, 1),
  * and for an odd last step; or one per four steps, as lbm_step does, until a
  * launch shape is set) covering every tile of every lattice (a workgroup
- * finds its lattice in a device table), and replays a captured HIP graph of eight steps for every full eight steps of a
+ * finds its lattice in a device table).  With one or two steps per launch it
+ * replays a captured HIP graph of eight steps for every full eight steps of a
  * call (not on the legacy null stream, which cannot be captured: there each
- * launch is made on its own).  Each lattice keeps its own workspace, state,
+ * launch is made on its own, as it is with four steps per launch).  Each lattice keeps its own workspace, state,
  * time counter and sticky error word, so lbm_moments, lbm_diagnostics,
  * lbm_sync and checkpointing work per handle as before, and results are
  * bitwise the same as stepping the handle alone.  A member may also be

@@ -601,8 +601,8 @@ hipError_t run_sweep2(lbm_handle *h, const void *src, void *dst)
     return hipErrorInvalidValue;
 }
 
-// kDeepSteps time steps in one pass.
-hipError_t run_four(lbm_handle *h, const void *src, void *dst)
+// kDeepSteps time steps in one pass, or 1 .. kDeepSteps in the block pass.
+hipError_t run_four(lbm_handle *h, const void *src, void *dst, int steps = kDeepSteps)
 {
     SweepArgs a = sweep_args(h, src, dst, Fields{}, true);
     a.tl = h->tiles4;
@@ -610,13 +610,13 @@ hipError_t run_four(lbm_handle *h, const void *src, void *dst)
     const bool block = h->shape4.block;
     switch (h->c.storage) {
     case LBM_STORE_F64:
-        return block ? launch_block<LBM_STORE_F64>(a) : launch_deep<LBM_STORE_F64>(a);
+        return block ? launch_block<LBM_STORE_F64>(a, steps) : launch_deep<LBM_STORE_F64>(a);
     case LBM_STORE_F32_SHIFTED:
-        return block ? launch_block<LBM_STORE_F32_SHIFTED>(a) : launch_deep<LBM_STORE_F32_SHIFTED>(a);
+        return block ? launch_block<LBM_STORE_F32_SHIFTED>(a, steps) : launch_deep<LBM_STORE_F32_SHIFTED>(a);
     case LBM_STORE_F16_SHIFTED:
-        return block ? launch_block<LBM_STORE_F16_SHIFTED>(a) : launch_deep<LBM_STORE_F16_SHIFTED>(a);
+        return block ? launch_block<LBM_STORE_F16_SHIFTED>(a, steps) : launch_deep<LBM_STORE_F16_SHIFTED>(a);
     case LBM_STORE_F16_LOCAL:
-        return block ? launch_block<LBM_STORE_F16_LOCAL>(a) : launch_deep<LBM_STORE_F16_LOCAL>(a);
+        return block ? launch_block<LBM_STORE_F16_LOCAL>(a, steps) : launch_deep<LBM_STORE_F16_LOCAL>(a);
     }
     return hipErrorInvalidValue;
 }
@@ -671,10 +671,17 @@ lbm_status read_sticky(lbm_handle *h)
 }
 
 
+// Whether a launch of `steps` steps is one of the long passes: kDeepSteps
+// steps, or 1 .. kDeepSteps in the block pass (as lbm_step takes them).
+bool batch_long(const lbm_batch *b, int steps)
+{
+    return steps == kDeepSteps || (b->total_tiles4 > 0 && b->shape4.block);
+}
+
 BatchArgs batch_args(const lbm_batch *b, int steps, const long long *ctr, long long steps_add,
                      int launches_add)
 {
-    const bool two = steps == 2, four = steps == kDeepSteps;
+    const bool four = batch_long(b, steps), two = steps == 2;
     return BatchArgs{b->d_table,
                      (int)b->members.size(),
                      ctr,
@@ -694,19 +701,19 @@ hipError_t batch_launch_steps(lbm_batch *b, int steps, const long long *ctr, lon
                               int launches_add)
 {
     const BatchArgs a = batch_args(b, steps, ctr, steps_add, launches_add);
-    if (steps == kDeepSteps) {
+    if (batch_long(b, steps)) {
         const bool block = b->shape4.block;
         switch (b->storage) {
         case LBM_STORE_F64:
-            return block ? launch_batch_block<LBM_STORE_F64>(a) : launch_batch_deep<LBM_STORE_F64>(a);
+            return block ? launch_batch_block<LBM_STORE_F64>(a, steps) : launch_batch_deep<LBM_STORE_F64>(a);
         case LBM_STORE_F32_SHIFTED:
-            return block ? launch_batch_block<LBM_STORE_F32_SHIFTED>(a)
+            return block ? launch_batch_block<LBM_STORE_F32_SHIFTED>(a, steps)
                          : launch_batch_deep<LBM_STORE_F32_SHIFTED>(a);
         case LBM_STORE_F16_SHIFTED:
-            return block ? launch_batch_block<LBM_STORE_F16_SHIFTED>(a)
+            return block ? launch_batch_block<LBM_STORE_F16_SHIFTED>(a, steps)
                          : launch_batch_deep<LBM_STORE_F16_SHIFTED>(a);
         case LBM_STORE_F16_LOCAL:
-            return block ? launch_batch_block<LBM_STORE_F16_LOCAL>(a)
+            return block ? launch_batch_block<LBM_STORE_F16_LOCAL>(a, steps)
                          : launch_batch_deep<LBM_STORE_F16_LOCAL>(a);
         }
         return hipErrorInvalidValue;
@@ -1077,11 +1084,17 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps)
     }
     int64_t k = 0;
     if (h->fuse == 2) {
-        for (; h->four && k + kDeepSteps <= nsteps; k += kDeepSteps) {
-            hipError_t e = run_four(h, h->cur, h->nxt);
+        while (h->four && k < nsteps) {
+            // the block pass takes the remainder of a call too (64^2 FP64: 3.8,
+            // 4.5 and 5.5 us for one to three steps, against 8, 10 and 18 in the
+            // other forms); the deep pass only whole groups
+            const int n = (int)std::min<int64_t>(kDeepSteps, nsteps - k);
+            if (n < kDeepSteps && !h->shape4.block) break;
+            hipError_t e = run_four(h, h->cur, h->nxt, n);
             if (e != hipSuccess) return dev_fail(h, e, "launching the four-step kernel");
             std::swap(h->cur, h->nxt);
-            h->t += kDeepSteps;
+            h->t += n;
+            k += n;
         }
         for (; k + 2 <= nsteps; k += 2) {
             hipError_t e = run_sweep2(h, h->cur, h->nxt);
@@ -1468,9 +1481,15 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps)
     }
     int64_t done = 0, launches = 0;
     const int per = batch_steps(b);
-    // the legacy null stream cannot be captured: there every launch is made
-    // on its own
-    const bool graphs = b->stream != nullptr;
+    // Graphs pay in the single- and two-step forms, whose launches on small
+    // lattices are shorter than the host's time per launch.  Four steps take 6
+    // us or more on the device and 2.8 us of launching: there the graph's
+    // counter kernel (one per eight steps) and its capture after every change
+    // of the table only cost (FP32 droplets, us per step with graphs and
+    // without: one of 64^2 2.42 and 1.62, twelve of 34 to 97 cells a side 3.15
+    // and 2.35, four of 500^2 10.6 and 9.8).  The legacy null stream cannot be
+    // captured either.
+    const bool graphs = b->stream != nullptr && per != kDeepSteps;
     if (graphs && nsteps >= kGraphSteps && !b->graph_valid) {
         const hipError_t e = batch_capture(b);
         if (e != hipSuccess) {
@@ -1498,7 +1517,11 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps)
         b->ctr_launches = l0 + kGraphSteps / per;
     }
     while (done < nsteps) {
-        const int k = nsteps - done >= per ? per : (nsteps - done >= batch_fuse(b) ? batch_fuse(b) : 1);
+        const int64_t left = nsteps - done;
+        const int k = left >= per ? per
+                                  : (batch_long(b, (int)left)     ? (int)left
+                                     : left >= batch_fuse(b) ? batch_fuse(b)
+                                                             : 1);
         const hipError_t e =
             batch_launch_steps(b, k, nullptr, b->steps_since_upload + done,
                                (int)((b->launches_since_upload + launches) & 1));
@@ -1557,6 +1580,7 @@ lbm_status lbm_batch_autotune(lbm_batch *b, double out[3])
     int bx2 = b->bx2, rows2 = b->rows2;
     if (try_two) {
         b->fuse_max = 2;
+        b->four = false;
         b->auto_rows2 = false;
         auto set = [&](const Shape &sh) {
             b->bx2 = sh.bx;

@@ -42,11 +42,12 @@ struct BlockLds {
 template <int ST, int RH>
 constexpr int kBlockWaves = (ST == LBM_STORE_F64 ? (RH == 32 ? 16 : 24) : 32) / (RH / 2) * (RH / 2) / 4;
 
-// Block `tile` of nbx x nby that a lattice is cut into.
+// Block `tile` of nbx x nby that a lattice is cut into, `steps` (1 .. T) steps:
+// fewer than T start as if the first T - steps had been taken.
 template <int RH, int T, int ST, int COLL>
 __device__ __forceinline__ void block_tile(const void *__restrict__ src_v, void *__restrict__ dst_v,
                                            const Coeffs &c, const Phys<typename Store<ST>::R> &P,
-                                           int nbx, int nby, int tile, long long t,
+                                           int nbx, int nby, int tile, long long t, int steps,
                                            unsigned long long *__restrict__ err)
 {
     using E = typename Store<ST>::E;
@@ -99,14 +100,14 @@ __device__ __forceinline__ void block_tile(const void *__restrict__ src_v, void 
     const int at = L::kGuard + (int)threadIdx.x;
     unsigned long long bad = ~0ull;
 #pragma unroll 1
-    for (int j = 0; j < T; ++j) {
+    for (int j = T - steps; j < T; ++j) {
         // rows whose values this step needs (whole waves leave the others out;
         // columns that are not needed are computed along)
         R rho = R(0), psi = R(0);
         if (ry >= 2 * j && ry < RH - 2 * j) {
             const bool ok = rho_psi<1, R>(g, ref, P, rho, psi);
             if (!ok && rx >= 2 * j && rx < ex - 2 * j && ry < ey - 2 * j)
-                bad = min(bad, domain_key(t + j, y, x, c.nx));
+                bad = min(bad, domain_key(t + (j - (T - steps)), y, x, c.nx));
             lds.psi[at] = psi;
         }
         __syncthreads();
@@ -190,29 +191,31 @@ __device__ __forceinline__ void block_tile(const void *__restrict__ src_v, void 
 template <int RH, int T, int ST, int COLL>
 __global__ __launch_bounds__(kBlockW *RH, (kBlockWaves<ST, RH>)) void block_kernel(
     const void *__restrict__ src, void *__restrict__ dst, Coeffs c,
-    Phys<typename Store<ST>::R> P, Tiles tl, long long t, unsigned long long *__restrict__ err)
+    Phys<typename Store<ST>::R> P, Tiles tl, long long t, int steps,
+    unsigned long long *__restrict__ err)
 {
     block_tile<RH, T, ST, COLL>(src, dst, c, P, tl.nstrips, tl.nseg,
-                                xcd_tile(blockIdx.x, tl.ntiles), t, err);
+                                xcd_tile(blockIdx.x, tl.ntiles), t, steps, err);
 }
 
 // The block pass over every lattice of a batch.
 template <int RH, int T, int ST, int COLL>
 __global__ __launch_bounds__(kBlockW *RH, (kBlockWaves<ST, RH>)) void batch_block_kernel(
     const BatchEntry *__restrict__ table, int nlat, const long long *__restrict__ d_ctr,
-    long long steps_add, int launches_add)
+    long long steps_add, int launches_add, int steps)
 {
     const BatchPos pos = batch_pos(d_ctr, steps_add, launches_add);
     const BatchTile k = batch_tile<&BatchEntry::tile0_4, &BatchEntry::tl4>(
         table, nlat, xcd_tile(blockIdx.x, gridDim.x), pos.steps, pos.parity);
     const auto P = in_scalar_registers(Phys<typename Store<ST>::R>(k.c));
-    block_tile<RH, T, ST, COLL>(k.src, k.dst, k.c, P, k.tl.nstrips, k.tl.nseg, k.tile, k.t, k.err);
+    block_tile<RH, T, ST, COLL>(k.src, k.dst, k.c, P, k.tl.nstrips, k.tl.nseg, k.tile, k.t,
+                                steps, k.err);
 }
 
 #define LBM_BLOCK_ROWS(X) X(16) X(20) X(24) X(32)
 
 template <int ST, int COLL>
-hipError_t block_launch_rows(const SweepArgs &a)
+hipError_t block_launch_rows(const SweepArgs &a, int steps)
 {
     const dim3 grid((unsigned)a.tl.ntiles);
     switch (a.bx) {
@@ -220,7 +223,7 @@ hipError_t block_launch_rows(const SweepArgs &a)
     case RH:                                                                                  \
         hipLaunchKernelGGL((block_kernel<RH, kDeepSteps, ST, COLL>), grid, dim3(kBlockW *RH), \
                            0, a.stream, a.src, a.dst, a.c,                                    \
-                           Phys<typename Store<ST>::R>(a.c), a.tl, a.t, a.err);               \
+                           Phys<typename Store<ST>::R>(a.c), a.tl, a.t, steps, a.err);        \
         break;
         LBM_BLOCK_ROWS(LBM_CASE)
 #undef LBM_CASE
@@ -231,21 +234,21 @@ hipError_t block_launch_rows(const SweepArgs &a)
 }
 
 template <int ST>
-hipError_t launch_block(const SweepArgs &a)
+hipError_t launch_block(const SweepArgs &a, int steps)
 {
-    return a.c.coll == LBM_COLL_MRT ? block_launch_rows<ST, LBM_COLL_MRT>(a)
-                                    : block_launch_rows<ST, LBM_COLL_BGK>(a);
+    return a.c.coll == LBM_COLL_MRT ? block_launch_rows<ST, LBM_COLL_MRT>(a, steps)
+                                    : block_launch_rows<ST, LBM_COLL_BGK>(a, steps);
 }
 
 template <int ST, int COLL>
-hipError_t batch_block_launch_rows(const BatchArgs &a)
+hipError_t batch_block_launch_rows(const BatchArgs &a, int steps)
 {
     switch (a.bx) {
 #define LBM_CASE(RH)                                                                          \
     case RH:                                                                                  \
         hipLaunchKernelGGL((batch_block_kernel<RH, kDeepSteps, ST, COLL>), dim3(a.grid),       \
                            dim3(kBlockW *RH), 0, a.stream, a.table, a.nlat, a.ctr,            \
-                           a.steps_add, a.launches_add);                                      \
+                           a.steps_add, a.launches_add, steps);                               \
         break;
         LBM_BLOCK_ROWS(LBM_CASE)
 #undef LBM_CASE
@@ -256,10 +259,10 @@ hipError_t batch_block_launch_rows(const BatchArgs &a)
 }
 
 template <int ST>
-hipError_t launch_batch_block(const BatchArgs &a)
+hipError_t launch_batch_block(const BatchArgs &a, int steps)
 {
-    return a.coll == LBM_COLL_MRT ? batch_block_launch_rows<ST, LBM_COLL_MRT>(a)
-                                  : batch_block_launch_rows<ST, LBM_COLL_BGK>(a);
+    return a.coll == LBM_COLL_MRT ? batch_block_launch_rows<ST, LBM_COLL_MRT>(a, steps)
+                                  : batch_block_launch_rows<ST, LBM_COLL_BGK>(a, steps);
 }
 
 }  // namespace lbmk

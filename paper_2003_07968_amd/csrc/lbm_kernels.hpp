@@ -1784,14 +1784,15 @@ constexpr int kHaloD = 2 * kDeepSteps - 1;  // halo columns and rows of a tile
 constexpr int kBlockW = 32, kBlockCols = kBlockW - 2 * kHaloD;
 template <int ST> hipError_t launch_deep(const SweepArgs &a);
 template <int ST> hipError_t launch_batch_deep(const BatchArgs &a);
-// Launchers of the block pass (lbm_block.hpp), likewise.
-template <int ST> hipError_t launch_block(const SweepArgs &a);
-template <int ST> hipError_t launch_batch_block(const BatchArgs &a);
+// Launchers of the block pass (lbm_block.hpp), likewise, for 1 .. kDeepSteps
+// steps.
+template <int ST> hipError_t launch_block(const SweepArgs &a, int steps);
+template <int ST> hipError_t launch_batch_block(const BatchArgs &a, int steps);
 #define LBM_DECLARE_FAMILY3(EXT, ST)                                                          \
     EXT template hipError_t launch_deep<ST>(const SweepArgs &);                               \
     EXT template hipError_t launch_batch_deep<ST>(const BatchArgs &);                         \
-    EXT template hipError_t launch_block<ST>(const SweepArgs &);                              \
-    EXT template hipError_t launch_batch_block<ST>(const BatchArgs &);
+    EXT template hipError_t launch_block<ST>(const SweepArgs &, int);                         \
+    EXT template hipError_t launch_batch_block<ST>(const BatchArgs &, int);
 #define LBM_EXTERN extern
 LBM_DECLARE_FAMILY1(LBM_EXTERN, LBM_STORE_F64)
 LBM_DECLARE_FAMILY1(LBM_EXTERN, LBM_STORE_F32_SHIFTED)
