@@ -8,6 +8,9 @@
 #include "lbm_probe.h"
 #include "lbm_kernels.hpp"
 
+#include <algorithm>
+#include <atomic>
+#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -28,10 +31,10 @@ __global__ void bump_counters(long long *p, long long steps, long long launches)
     p[1] += launches;
 }
 
-// Second stage of the diagnostics: one workgroup sums the per-tile partials
-// in a fixed order.
-__global__ __launch_bounds__(256) void reduce_partials(const double *__restrict__ partials,
-                                                        int ntiles, double *__restrict__ out)
+// Second stage of the diagnostics: one workgroup of 256 sums the per-tile
+// partials in a fixed order.
+__device__ __forceinline__ void reduce_tiles(const double *__restrict__ partials, int ntiles,
+                                             double *__restrict__ out)
 {
     __shared__ double red[4];
     double acc[kDiag] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -53,6 +56,39 @@ __global__ __launch_bounds__(256) void reduce_partials(const double *__restrict_
     }
 }
 
+__global__ __launch_bounds__(256) void reduce_partials(const double *__restrict__ partials,
+                                                        int ntiles, double *__restrict__ out)
+{
+    reduce_tiles(partials, ntiles, out);
+}
+
+// Diagnostics without the copies: the reduced values and the lattice's error
+// word, written to page-locked host memory (out: kDiag doubles, then the word).
+__global__ __launch_bounds__(256) void reduce_partials_host(const double *__restrict__ partials,
+                                                             int ntiles,
+                                                             const unsigned long long *err,
+                                                             double *__restrict__ out)
+{
+    reduce_tiles(partials, ntiles, out);
+    if (threadIdx.x == 0) ((unsigned long long *)out)[kDiag] = *err;
+}
+
+// Error words of up to kHostWords lattices to page-locked host memory.
+constexpr int kHostWords = 32;
+struct ErrorWords {
+    const unsigned long long *p[kHostWords];
+};
+
+__global__ void publish_errors(ErrorWords w, int n, unsigned long long *out)
+{
+    const int k = threadIdx.x;
+    if (k < n) out[k] = *w.p[k];
+}
+
+__global__ void publish_error(const unsigned long long *err, unsigned long long *out)
+{
+    *out = *err;
+}
 
 __global__ void fill_u64(unsigned long long *p, unsigned long long v) { *p = v; }
 
@@ -132,6 +168,72 @@ hipError_t scratch_on_device(int dev, double **out)
     *out = g_scratch_ptr[dev];
     return hipSuccess;
 }
+}  // namespace
+
+// ---- Host words ----
+//
+// Where the calls that wait for the stream read their small results (error
+// words, diagnostics): a kernel writes them to page-locked host memory, the
+// host reads them after its one wait.  A copy to the caller's pageable memory
+// costs a staging copy and a second wait in the runtime (lbm_sync of an idle
+// stream: 20 us with the copy, WITH_WORDS us with the words).
+//
+// One page of kHostSlots slots of kHostWords words for the whole process,
+// allocated at the first use and kept; a call holds a slot from its launch to
+// the end of its wait.  Without a page or a free slot (more than kHostSlots
+// calls at once) the calls use the copies.  A slot whose wait failed is not
+// used again: a kernel may still write to it.
+namespace {
+constexpr int kHostSlots = 16;
+std::once_flag g_host_once;
+unsigned long long *g_host_page;  // null: none
+std::atomic<uint32_t> g_host_busy{0};
+
+struct HostWords {
+    unsigned long long *w = nullptr;  // null: no slot
+    int slot = 0;
+
+    HostWords() = default;
+    HostWords(const HostWords &) = delete;
+    HostWords &operator=(const HostWords &) = delete;
+
+    // Take a slot for work on a stream of device `dev`.
+    explicit HostWords(int dev)
+    {
+        int cur = -1;
+        // a launch needs the stream's device current, which a copy does not
+        if (hipGetDevice(&cur) != hipSuccess || cur != dev) return;
+        std::call_once(g_host_once, [] {
+            // allocating is allowed while another thread captures a graph
+            // in the global mode only with this thread's mode relaxed
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
+            void *p = nullptr;
+            if (hipHostMalloc(&p, kHostSlots * kHostWords * sizeof(*g_host_page),
+                              hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+                g_host_page = (unsigned long long *)p;
+            else
+                (void)hipGetLastError();
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+        });
+        if (!g_host_page) return;
+        uint32_t busy = g_host_busy.load(std::memory_order_relaxed);
+        do {
+            const uint32_t open = ~busy & ((1u << kHostSlots) - 1u);
+            if (open == 0) return;
+            slot = __builtin_ctz(open);
+        } while (!g_host_busy.compare_exchange_weak(busy, busy | (1u << slot),
+                                                    std::memory_order_acquire));
+        w = g_host_page + (size_t)slot * kHostWords;
+    }
+
+    // After a successful wait for the work that wrote the slot.
+    void give_back()
+    {
+        if (w) g_host_busy.fetch_and(~(1u << slot), std::memory_order_release);
+        w = nullptr;
+    }
+};
 }  // namespace
 
 struct lbm_batch {
@@ -651,12 +753,9 @@ hipError_t run_permute(lbm_handle *h, const void *in, void *out, int to_canonica
     return hipErrorInvalidValue;
 }
 
-lbm_status read_sticky(lbm_handle *h)
+// The handle's status by its error word as read back.
+lbm_status set_sticky(lbm_handle *h, unsigned long long key)
 {
-    unsigned long long key = ~0ull;
-    hipError_t e = hipMemcpyAsync(&key, h->err, sizeof(key), hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    if (e != hipSuccess) return dev_fail(h, e, "reading the error word");
     if (key != ~0ull) {
         const long long step = (long long)(key >> 32);
         const long long cell = (long long)(key & 0xffffffffull);
@@ -668,6 +767,29 @@ lbm_status read_sticky(lbm_handle *h)
         h->sticky = LBM_ERR_DOMAIN;
     }
     return h->sticky;
+}
+
+// Wait for the stream and read the error word with a copy.
+lbm_status read_sticky_copy(lbm_handle *h)
+{
+    unsigned long long key = ~0ull;
+    hipError_t e = hipMemcpyAsync(&key, h->err, sizeof(key), hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) return dev_fail(h, e, "reading the error word");
+    return set_sticky(h, key);
+}
+
+lbm_status read_sticky(lbm_handle *h)
+{
+    HostWords host(h->device);
+    if (!host.w) return read_sticky_copy(h);
+    hipLaunchKernelGGL(publish_error, dim3(1), dim3(1), 0, h->stream, h->err, host.w);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) return dev_fail(h, e, "reading the error word");
+    const unsigned long long key = host.w[0];
+    host.give_back();
+    return set_sticky(h, key);
 }
 
 
@@ -1133,6 +1255,19 @@ lbm_status lbm_diagnostics(lbm_handle *h, double out[6])
     if (!h || !out) return LBM_ERR_INVALID_ARG;
     hipError_t e = run_sweep<kDiagnostics>(h, h->cur, nullptr, Fields{});
     if (e != hipSuccess) return dev_fail(h, e, "launching the diagnostics kernel");
+    HostWords host(h->device);
+    if (host.w) {
+        hipLaunchKernelGGL(reduce_partials_host, dim3(1), dim3(256), 0, h->stream, h->partials,
+                           h->tiles.ntiles, h->err, (double *)host.w);
+        e = hipGetLastError();
+        if (e != hipSuccess) return dev_fail(h, e, "launching the reduction kernel");
+        e = hipStreamSynchronize(h->stream);
+        if (e != hipSuccess) return dev_fail(h, e, "reading the diagnostics");
+        std::memcpy(out, host.w, kDiag * sizeof(double));
+        const unsigned long long key = host.w[kDiag];
+        host.give_back();
+        return set_sticky(h, key);
+    }
     hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(256), 0, h->stream, h->partials,
                        h->tiles.ntiles, h->diag_out);
     e = hipGetLastError();
@@ -1140,7 +1275,7 @@ lbm_status lbm_diagnostics(lbm_handle *h, double out[6])
     e = hipMemcpyAsync(out, h->diag_out, kDiag * sizeof(double), hipMemcpyDeviceToHost,
                        h->stream);
     if (e != hipSuccess) return dev_fail(h, e, "copying diagnostics");
-    return read_sticky(h);
+    return read_sticky_copy(h);
 }
 
 lbm_status lbm_diagnostics_noalloc(lbm_handle *h, double out[6])
@@ -1174,7 +1309,8 @@ lbm_status lbm_diagnostics_noalloc(lbm_handle *h, double out[6])
             e = hipMemcpyAsync(out, red, kDiag * sizeof(double), hipMemcpyDeviceToHost,
                                h->stream);
     }
-    lbm_status st = e == hipSuccess ? read_sticky(h)
+    // (read_sticky may allocate host memory at its first use)
+    lbm_status st = e == hipSuccess ? read_sticky_copy(h)
                                     : dev_fail(h, e, "diagnostics with the static scratch");
     if (prev != h->device) (void)hipSetDevice(prev);
     return st;
@@ -1745,6 +1881,30 @@ lbm_status lbm_probe_stream(const double *d_src, double *d_dst, int32_t nx, int3
 }  // extern "C"
 
 namespace lbm_internal {
+
+void read_errors(lbm_handle *const *h, int n, lbm_status *st)
+{
+    for (int k0 = 0; k0 < n; k0 += kHostWords) {
+        const int m = std::min(kHostWords, n - k0);
+        HostWords host(h[k0]->device);
+        if (!host.w) {
+            for (int k = 0; k < m; ++k)
+                st[k0 + k] = read_sticky_copy(h[k0 + k]);
+            continue;
+        }
+        ErrorWords w{};
+        for (int k = 0; k < m; ++k)
+            w.p[k] = h[k0 + k]->err;
+        const hipStream_t stream = h[k0]->stream;
+        hipLaunchKernelGGL(publish_errors, dim3(1), dim3(64), 0, stream, w, m, host.w);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = hipStreamSynchronize(stream);
+        for (int k = 0; k < m; ++k)
+            st[k0 + k] = e == hipSuccess ? set_sticky(h[k0 + k], host.w[k])
+                                         : dev_fail(h[k0 + k], e, "reading the error words");
+        if (e == hipSuccess) host.give_back();
+    }
+}
 
 lbm_status enqueue_density(lbm_handle *h, double *d_rho)
 {

@@ -16,4 +16,9 @@ __attribute__((visibility("hidden"))) lbm_status enqueue_density(lbm_handle *h, 
 __attribute__((visibility("hidden"))) lbm_status enqueue_populations(lbm_handle *h,
                                                                      double *d_f);
 
+// lbm_sync of n lattices of one stream: st[k] is what lbm_sync(h[k]) returns.
+// One launch and one wait for every 32 lattices, not a copy and a wait each.
+__attribute__((visibility("hidden"))) void read_errors(lbm_handle *const *h, int n,
+                                                       lbm_status *st);
+
 }  // namespace lbm_internal

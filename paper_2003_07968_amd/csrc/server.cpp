@@ -171,8 +171,19 @@ lbm_status step_batches(lbm_server *s)
     return LBM_OK;
 }
 
-// Retire the finished jobs.  The stream is drained once, after which every
-// finishing job's sticky error is read; the outputs of those without one
+// Status of each job's lattice (lbm_sync's) once the stream has drained.
+std::vector<lbm_status> statuses(const std::vector<Job *> &jobs)
+{
+    std::vector<lbm_handle *> h;
+    for (const Job *j : jobs)
+        h.push_back(j->h);
+    std::vector<lbm_status> st(jobs.size(), LBM_ERR_DEVICE);
+    lbm_internal::read_errors(h.data(), (int)h.size(), st.data());
+    return st;
+}
+
+// Retire the finished jobs.  The stream is drained once, with every
+// finishing job's sticky error; the outputs of those without one
 // (density, populations) are then enqueued with their copies to the caller's
 // host buffers, and the stream is drained once more.  A round that retires
 // many jobs therefore waits twice in all, not once per job and output.
@@ -190,13 +201,14 @@ lbm_status retire(lbm_server *s, int32_t *n_retired)
     }
     if (n_retired) *n_retired = (int32_t)done.size();
     if (done.empty()) return LBM_OK;
-    bool device_ok = hipStreamSynchronize(s->stream) == hipSuccess;
+    const std::vector<lbm_status> own = statuses(done);
+    bool device_ok = std::find(own.begin(), own.end(), LBM_ERR_DEVICE) == own.end();
     std::vector<lbm_status> st(done.size(), LBM_ERR_DEVICE);
     bool copies = false;
     for (size_t k = 0; k < done.size() && device_ok; ++k) {
         Job *j = done[k];
         st[k] = lbm_batch_remove(s->batches[j->key], j->h);
-        if (st[k] == LBM_OK) st[k] = lbm_sync(j->h);
+        if (st[k] == LBM_OK) st[k] = own[k];
         if (st[k] != LBM_OK) continue;
         double *d_buf = (double *)(s->arena_base + j->buf_off);
         const size_t nc = cells(j->p);
@@ -234,18 +246,19 @@ lbm_status retire(lbm_server *s, int32_t *n_retired)
 lbm_status retire_failed(lbm_server *s, int32_t *n_retired)
 {
     int32_t n = 0;
-    if (hipStreamSynchronize(s->stream) != hipSuccess) return LBM_ERR_DEVICE;
-    for (size_t k = 0; k < s->resident.size();) {
+    if (s->resident.empty() && hipStreamSynchronize(s->stream) != hipSuccess)
+        return LBM_ERR_DEVICE;
+    const std::vector<lbm_status> st = statuses(s->resident);
+    for (size_t k = 0, at = 0; at < st.size(); ++at) {
         Job *j = s->resident[k];
-        const lbm_status st = lbm_sync(j->h);
-        if (st == LBM_OK) {
+        if (st[at] == LBM_OK) {
             ++k;
             continue;
         }
-        if (st != LBM_ERR_DOMAIN) return LBM_ERR_DEVICE;
+        if (st[at] != LBM_ERR_DOMAIN) return LBM_ERR_DEVICE;
         s->resident.erase(s->resident.begin() + (long)k);
         if (lbm_batch_remove(s->batches[j->key], j->h) != LBM_OK) return LBM_ERR_DEVICE;
-        finish(s, j, st);
+        finish(s, j, st[at]);
         ++n;
     }
     if (n_retired) *n_retired = n;
