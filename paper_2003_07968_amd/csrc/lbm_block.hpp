@@ -125,7 +125,7 @@ __device__ __forceinline__ void block_tile(const void *__restrict__ src_v, void 
             force<R>(s, P, Fx, Fy);
             velocity<R>(g, rho, Fx, Fy, ux, uy, Jx, Jy);
             if constexpr (COLL == LBM_COLL_MRT)
-                collide_mrt<R>(g, rho, ux, uy, Fx, Fy, P);
+                collide_mrt<R>(g, rho, ux, uy, Jx, Jy, Fx, Fy, P);
             else
                 collide<R>(g, ref, rho, ux, uy, Jx, Jy, Fx, Fy, P);
             // rounded as a single step stores it

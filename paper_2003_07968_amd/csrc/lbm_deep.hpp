@@ -274,7 +274,7 @@ __device__ __forceinline__ void deep_stage(
             const R ref = LOC ? refs[J % 2] : gref;
             velocity<R>(h, C.rho, Fx, Fy, ux, uy, Jx, Jy);
             if constexpr (COLL == LBM_COLL_MRT)
-                collide_mrt<R>(h, C.rho, ux, uy, Fx, Fy, P);
+                collide_mrt<R>(h, C.rho, ux, uy, Jx, Jy, Fx, Fy, P);
             else
                 collide<R>(h, ref, C.rho, ux, uy, Jx, Jy, Fx, Fy, P);
             E X[kQ];

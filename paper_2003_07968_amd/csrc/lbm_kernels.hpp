@@ -127,6 +127,19 @@ struct Coeffs {
     int8_t force_on, trace_alt, storage;
 };
 
+// The forms of the force, the velocity and the collisions with the fewest
+// operations, for FP64 (BGK: 114 FP64 instructions per cell and step where the
+// forms written next to them take 143; 2048 x 8192 cells 128 -> 119 us per
+// step in the deep pass).  They round differently from those, by a few 1e-16
+// of the values; against the equations in 80 bits, over 24 lattices of 40 to
+// 110 cells a side and 20 to 120 steps, the populations are off by 3.5e-15
+// (BGK, rms; 9.3e-15 in the other forms) and 6.4e-15 (MRT; 6.3e-15).  The
+// modes that store rounded populations keep the other forms: there a last bit
+// decides which way a stored value rounds, so results would change by the
+// storage's precision.
+template <class R>
+constexpr bool kFewerOps = std::is_same_v<R, double>;
+
 // The coefficients in the arithmetic type of a storage mode.
 // tr0, tr1, tr2: the trace M2_bb as tr0 psi_0 + tr1 (psi_1 + .. + psi_4) +
 // tr2 (psi_5 + .. + psi_8), the direct trace of Eq. SOMED (-8, 1, 1)/27 or
@@ -143,6 +156,11 @@ struct Phys {
     R m3g, om2;                       // -3 guo, omega/2 (collide)
     // collide_mrt: 1 - s and 1 - s/2 of each rate (n: omega, the stress rows)
     R ke, he, kz, hz, kq, hq, kn, hn;
+    // kFewerOps: force's weights of s0, s58, s13 and s24 with G0 in them,
+    // omega/9 and omega/36, 6 he, 6 hz and 2 hn.  keep is 1 - 9 (omega/9) with
+    // the rounded omega/9 there: the weights of d and rho in the collision sum
+    // to one, and the mass does not drift by omega/9's rounding.
+    R h_0, h_58, h_2, h_1, om9, om36, he6, hz6, hn2;
     Phys() = default;
     __host__ __device__ explicit Phys(const Coeffs &c)
         : omega((R)c.omega), guo((R)c.guo), eos_b((R)c.eos_b), kcT((R)c.kcT), ka((R)c.ka),
@@ -155,10 +173,13 @@ struct Phys {
           t0((R)((c.cSC + c.cB * (c.trace_alt ? -10.0 / 27.0 : -8.0 / 27.0)) / 9.0)),
           t1((R)(c.cB * (c.trace_alt ? 2.0 / 27.0 : 1.0 / 27.0) / 9.0)),
           t2((R)(c.cB * (c.trace_alt ? 1.0 / 54.0 : 1.0 / 27.0) / 9.0)),
-          keep((R)(1.0 - c.omega)), om3((R)(c.omega / 3.0)), g3((R)(c.guo / 3.0)),
+          keep(kFewerOps<R> ? (R)fma(-9.0, c.omega / 9.0, 1.0) : (R)(1.0 - c.omega)),
+          om3((R)(c.omega / 3.0)), g3((R)(c.guo / 3.0)),
           m3g(R(-3) * guo), om2(R(0.5) * omega), ke(R(1) - s_e), he(R(1) - R(0.5) * s_e),
           kz(R(1) - s_z), hz(R(1) - R(0.5) * s_z), kq(R(1) - s_q), hq(R(1) - R(0.5) * s_q),
-          kn(R(1) - omega), hn(R(1) - R(0.5) * omega)
+          kn(R(1) - omega), hn(R(1) - R(0.5) * omega), h_0(t0 + m2_0), h_58(t2 + m2_58),
+          h_2(t1 + m2_2), h_1(t1 + m2_1), om9((R)(c.omega / 9.0)), om36((R)(c.omega / 36.0)),
+          he6(R(6) * he), hz6(R(6) * hz), hn2(R(2) * hn)
     {
     }
 };
@@ -289,43 +310,43 @@ __device__ __forceinline__ void reconstruct(R d[kQ], const Tri<R> &D, const Tri<
     d[8] = fma(w2, U.l - ref, d[8]);
 }
 
-// Reciprocal and quotient in the arithmetic type.  FP64: the hardware
-// reciprocal estimate refined by two Newton steps (x <- x + x (1 - v x), each
-// doubling the correct bits), and the quotient corrected once by its residual
-// (q <- q + (a - b q) / b), within about one ulp of the rounded result and
-// with a shorter dependent chain than the IEEE division sequence; the
+// Reciprocal, quotient and square root in the arithmetic type.  FP32: the
+// hardware's single-instruction forms, whose error of about one ulp is far
+// below the storage rounding of the reduced-precision modes.  FP64: from the
+// hardware estimates (relative error e0 of 2^-24.2, measured), with no more steps
+// than full precision needs, as the step is bound by its instruction count;
 // arguments are well scaled (rho and (1 - b rho)^3 inside the EOS domain).
-// FP32: the hardware's single-instruction forms, whose error of about one ulp
-// is far below the storage rounding of the reduced-precision modes.
+//   reciprocal: x (1 + e + e^2), e = 1 - v x, leaves e0^3;
+//   quotient: one Newton step of the reciprocal leaves e0^2, the quotient's
+//     correction by its residual (q <- q + (a - b q) x) the product of both;
+//   square root (v >= 0 by the EOS domain check; 0 gives 0): y ~ 1/sqrt(v),
+//     g = v y refined once (r = 1/2 - g y/2; g += g r) leaves 1.5 e0^2, its
+//     correction by the residual (g += (v - g g) y/2) the product with e0.
+// Over 2^21 arguments of 2^-12 to 2^4 each is within 0.500001 ulp and rounds
+// 0.02% of them the other way, as the forms with one refinement more do.
 __device__ __forceinline__ double recip(double v)
 {
-    double x = __builtin_amdgcn_rcp(v);
-    x = fma(x, fma(-v, x, 1.0), x);
-    return fma(x, fma(-v, x, 1.0), x);
+    const double x = __builtin_amdgcn_rcp(v);
+    const double e = fma(-v, x, 1.0);
+    return fma(x, fma(e, e, e), x);
 }
 __device__ __forceinline__ float recip(float v) { return __builtin_amdgcn_rcpf(v); }
 __device__ __forceinline__ double quot(double a, double b)
 {
-    const double x = recip(b);
+    double x = __builtin_amdgcn_rcp(b);
+    x = fma(x, fma(-b, x, 1.0), x);
     const double q = a * x;
     return fma(fma(-b, q, a), x, q);
 }
 __device__ __forceinline__ float quot(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
-// Square root: FP64 from the hardware reciprocal-square-root estimate y,
-// g = v y and h = y/2 refined together (r = 1/2 - g h; g += g r; h += h r),
-// then g corrected twice by its residual (g += (v - g g) h), within about one
-// ulp; v >= 0 here (the EOS domain check), and v = 0 gives 0.  FP32: the
-// single-instruction form.
 __device__ __forceinline__ double root(double v)
 {
-    const double y = __builtin_amdgcn_rsq(v);
-    double g = v * y, h = 0.5 * y;
-    const double r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    g = fma(fma(-g, g, v), h, g);
-    g = fma(fma(-g, g, v), h, g);
-    return v > 0.0 ? g : v;
+    // (an estimate for the smallest normal number in place of 0's infinity)
+    const double y = __builtin_amdgcn_rsq(fmax(v, 0x1p-1022));
+    const double h = 0.5 * y;
+    double g = v * y;
+    g = fma(g, fma(-g, h, 0.5), g);
+    return fma(fma(-g, g, v), h, g);
 }
 __device__ __forceinline__ float root(float v) { return __builtin_amdgcn_sqrtf(v); }
 
@@ -384,7 +405,9 @@ __device__ __forceinline__ unsigned long long domain_key(long long t, int r, int
 //   F_a = cSC s0 M1_a + cA M1_b M2_ab + cB tr M1_a.
 // Evaluated as F_a = G0 N_a + N_b Q_ab with N = 9 M1 = (s1 - s3) + (a - b)/4,
 // Q = cA M2/9 and G0 = (cSC s0 + cB tr)/9, the constant factors folded into
-// the weights (Phys), each combination of psi values with multiply-adds.
+// the weights (Phys), each combination of psi values with multiply-adds.  In
+// FP64 G0 is folded into the diagonal of Q as well (H = G0 + Q, six
+// operations less).
 template <class R>
 __device__ __forceinline__ void force(const R s[kQ], const Phys<R> &P, R &Fx, R &Fy)
 {
@@ -395,6 +418,15 @@ __device__ __forceinline__ void force(const R s[kQ], const Phys<R> &P, R &Fx, R 
     const R s58 = p57 + p68;
     const R Nx = fma(R(0.25), a57 - b68, d13);
     const R Ny = fma(R(0.25), a57 + b68, d24);
+    if constexpr (kFewerOps<R>) {
+        const R h0 = fma(P.h_0, s[0], P.h_58 * s58);
+        const R Hxx = fma(P.h_2, s13, fma(P.h_1, s24, h0));
+        const R Hyy = fma(P.h_2, s24, fma(P.h_1, s13, h0));
+        const R Hxy = (p57 - p68) * P.m2_xy;
+        Fx = fma(Nx, Hxx, Ny * Hxy);
+        Fy = fma(Ny, Hyy, Nx * Hxy);
+        return;
+    }
     const R q0 = fma(P.m2_0, s[0], P.m2_58 * s58);
     const R Qxx = fma(P.m2_2, s13, fma(P.m2_1, s24, q0));
     const R Qyy = fma(P.m2_2, s24, fma(P.m2_1, s13, q0));
@@ -411,8 +443,15 @@ template <class R>
 __device__ __forceinline__ void velocity(const R d[kQ], R rho, R Fx, R Fy, R &ux, R &uy, R &Jx,
                                          R &Jy)
 {
-    const R jx = ((d[1] - d[3]) + (d[5] - d[6])) + (d[8] - d[7]);
-    const R jy = ((d[2] - d[4]) + (d[5] + d[6])) - (d[7] + d[8]);
+    R jx, jy;
+    if constexpr (kFewerOps<R>) {
+        const R a57 = d[5] - d[7], b68 = d[6] - d[8];
+        jx = (d[1] - d[3]) + (a57 - b68);
+        jy = (d[2] - d[4]) + (a57 + b68);
+    } else {
+        jx = ((d[1] - d[3]) + (d[5] - d[6])) + (d[8] - d[7]);
+        jy = ((d[2] - d[4]) + (d[5] + d[6])) - (d[7] + d[8]);
+    }
     const R inv = recip(rho);
     Jx = fma(R(0.5), Fx, jx);
     Jy = fma(R(0.5), Fy, jy);
@@ -435,11 +474,38 @@ __device__ __forceinline__ void velocity(const R d[kQ], R rho, R Fx, R Fy, R &ux
 // weight / 4, an exact scaling.  Multiply-adds are written as explicit fma();
 // the file is compiled without implicit contraction, so every inlined copy
 // rounds the same way.
+//
+// With q = (omega/2) J + g F the axis terms are w (c.u)(h c.u + m c.F) = c.u c.q
+// = u_x q_x or u_y q_y, and with S = u_x q_x + u_y q_y the isotropic part is
+// w A = omega rho/9 - S/3, the diagonal pairs' T = omega rho/36 + S/6 +-
+// (u_x q_y + u_y q_x)/4: 17 operations less (kFewerOps).
 template <class R>
 __device__ __forceinline__ void collide(R d[kQ], R ref, R rho, R ux, R uy, R Jx, R Jy, R Fx,
                                         R Fy, const Phys<R> &P)
 {
     const R om = P.omega, g = P.guo, keep = P.keep;
+    if constexpr (kFewerOps<R>) {
+        const R gx = g * Fx, gy = g * Fy;
+        const R qx = fma(P.om2, Jx, gx), qy = fma(P.om2, Jy, gy);
+        const R Bx = fma(om, Jx, gx), By = fma(om, Jy, gy);  // B/3
+        const R Ex = ux * qx, Ey = uy * qy, S = Ex + Ey;
+        const R cross = fma(ux, qy, uy * qx);
+        const R A1 = fma(R(-1.0 / 3.0), S, P.om9 * rho);
+        const R W = fma(R(1.0 / 6.0), S, P.om36 * rho);
+        const R Tx = Ex + A1, Ty = Ey + A1;
+        const R T5 = fma(R(0.25), cross, W), T6 = fma(R(-0.25), cross, W);
+        const R B5 = Bx + By, B6 = By - Bx;
+        d[0] = fma(R(4), A1, keep * d[0]);
+        d[1] = fma(keep, d[1], fma(R(1.0 / 3.0), Bx, Tx));
+        d[3] = fma(keep, d[3], fma(R(-1.0 / 3.0), Bx, Tx));
+        d[2] = fma(keep, d[2], fma(R(1.0 / 3.0), By, Ty));
+        d[4] = fma(keep, d[4], fma(R(-1.0 / 3.0), By, Ty));
+        d[5] = fma(keep, d[5], fma(R(1.0 / 12.0), B5, T5));
+        d[7] = fma(keep, d[7], fma(R(-1.0 / 12.0), B5, T5));
+        d[6] = fma(keep, d[6], fma(R(1.0 / 12.0), B6, T6));
+        d[8] = fma(keep, d[8], fma(R(-1.0 / 12.0), B6, T6));
+        return;
+    }
     const R usq = fma(ux, ux, uy * uy);
     const R uF = fma(ux, Fx, uy * Fy);
     const R A = fma(om, fma(rho, R(-1.5) * usq, kNoRef<R> ? rho : rho - ref), P.m3g * uF);
@@ -456,12 +522,12 @@ __device__ __forceinline__ void collide(R d[kQ], R ref, R rho, R ux, R uy, R Jx,
     d[2] = fma(keep, d[2], Ty + By);
     d[4] = fma(keep, d[4], Ty - By);
     // diagonal directions (w = 1/36): directions 5/7 along (1, 1), 6/8 along (-1, 1)
-    const R A2 = R(0.25) * A1, h2 = R(0.25) * h1;
+    // (the 1/4 taken out of the sums: exact, so no rounding moves)
     const R u5 = ux + uy, u6 = uy - ux;
-    const R m5 = R(0.25) * (mx + my), m6 = R(0.25) * (my - mx);
-    const R B5 = R(0.25) * (Bx + By), B6 = R(0.25) * (By - Bx);
-    const R T5 = fma(u5, fma(h2, u5, m5), A2);
-    const R T6 = fma(u6, fma(h2, u6, m6), A2);
+    const R T5 = R(0.25) * fma(u5, fma(h1, u5, mx + my), A1);
+    const R T6 = R(0.25) * fma(u6, fma(h1, u6, my - mx), A1);
+    const R By4 = R(0.25) * By;
+    const R B5 = fma(R(0.25), Bx, By4), B6 = fma(R(-0.25), Bx, By4);
     d[5] = fma(keep, d[5], T5 + B5);
     d[7] = fma(keep, d[7], T5 - B5);
     d[6] = fma(keep, d[6], T6 + B6);
@@ -480,9 +546,48 @@ __device__ __forceinline__ void collide(R d[kQ], R ref, R rho, R ux, R uy, R Jx,
 // The rows of M are orthogonal, so M^-1 = M^T diag(1/9, 1/36, 1/36, 1/6, 1/12,
 // 1/6, 1/12, 1/4, 1/4).
 template <class R>
-__device__ __forceinline__ void collide_mrt(R d[kQ], R rho, R ux, R uy, R Fx, R Fy,
-                                            const Phys<R> &P)
+__device__ __forceinline__ void collide_mrt(R d[kQ], R rho, R ux, R uy, R Jx, R Jy,
+                                            R Fx, R Fy, const Phys<R> &P)
 {
+    if constexpr (kFewerOps<R>) {
+        // sums and differences of opposite pairs shared by the moments (the
+        // momentum's with velocity()), rho u = J, and the stress rows' r =
+        // omega J + 2 (1 - omega/2) F: 31 operations less
+        const R s13 = d[1] + d[3], s24 = d[2] + d[4], s57 = d[5] + d[7], s68 = d[6] + d[8];
+        const R d13 = d[1] - d[3], d24 = d[2] - d[4], a57 = d[5] - d[7], b68 = d[6] - d[8];
+        const R ax = s13 + s24, dg = s57 + s68, px = a57 - b68, py = a57 + b68;
+        const R dr = d[0] + (ax + dg);
+        const R e = fma(R(-4), d[0], fma(R(2), dg, -ax));
+        const R z = fma(R(4), d[0], fma(R(-2), ax, dg));
+        const R uF = fma(ux, Fx, uy * Fy);
+        const R r3 = R(3) * fma(ux, Jx, uy * Jy);
+        const R es = fma(P.ke, e, fma(P.s_e, fma(R(-2), dr, r3), P.he6 * uF));
+        const R zs = fma(P.kz, z, fma(P.s_z, dr - r3, -P.hz6 * uF));
+        const R jxs = (d13 + px) + Fx, jys = (d24 + py) + Fy;
+        const R qxs = fma(P.kq, fma(R(-2), d13, px), -fma(P.s_q, Jx, P.hq * Fx));
+        const R qys = fma(P.kq, fma(R(-2), d24, py), -fma(P.s_q, Jy, P.hq * Fy));
+        const R rx = fma(P.omega, Jx, P.hn2 * Fx), ry = fma(P.omega, Jy, P.hn2 * Fy);
+        const R pxxs = fma(P.kn, s13 - s24, fma(ux, rx, -(uy * ry)));
+        const R pxys = fma(R(0.5), fma(ux, ry, uy * rx), P.kn * (s57 - s68));
+        const R r9 = dr * R(1.0 / 9.0);
+        const R A1 = fma(es, R(-1.0 / 36.0), fma(zs, R(-1.0 / 18.0), r9));
+        const R A2 = fma(es, R(1.0 / 18.0), fma(zs, R(1.0 / 36.0), r9));
+        const R xa = jxs - qxs, ya = jys - qys;
+        const R xd = fma(R(2), jxs, qxs), yd = fma(R(2), jys, qys);
+        const R Bx = fma(R(0.25), pxxs, A1), By = fma(R(-0.25), pxxs, A1);
+        const R B5 = fma(R(0.25), pxys, A2), B6 = fma(R(-0.25), pxys, A2);
+        const R v5 = xd + yd, v6 = yd - xd;
+        d[0] = fma(zs - es, R(1.0 / 9.0), r9);
+        d[1] = fma(R(1.0 / 6.0), xa, Bx);
+        d[3] = fma(R(-1.0 / 6.0), xa, Bx);
+        d[2] = fma(R(1.0 / 6.0), ya, By);
+        d[4] = fma(R(-1.0 / 6.0), ya, By);
+        d[5] = fma(R(1.0 / 12.0), v5, B5);
+        d[7] = fma(R(-1.0 / 12.0), v5, B5);
+        d[6] = fma(R(1.0 / 12.0), v6, B6);
+        d[8] = fma(R(-1.0 / 12.0), v6, B6);
+        return;
+    }
     const R dr = (((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7]))) + d[8];
     const R ax = (d[1] + d[2]) + (d[3] + d[4]);             // axis directions
     const R dg = (d[5] + d[6]) + (d[7] + d[8]);             // diagonal directions
@@ -765,7 +870,7 @@ __device__ __forceinline__ void walk(const typename Store<ST>::E *__restrict__ s
         const size_t row = (size_t)y * c.nx;
         if (MODE == kStep) {
             if constexpr (COLL == LBM_COLL_MRT)
-                collide_mrt<R>(f[cur], C.rho, ux, uy, Fx, Fy, P);
+                collide_mrt<R>(f[cur], C.rho, ux, uy, Jx, Jy, Fx, Fy, P);
             else
                 collide<R>(f[cur], ref_cur, C.rho, ux, uy, Jx, Jy, Fx, Fy, P);
             if (interior) {
@@ -1260,7 +1365,7 @@ __device__ __forceinline__ void walk2(const typename Store<ST>::E *__restrict__ 
             R ux, uy, Jx, Jy;
             velocity<R>(g, rho, Fx, Fy, ux, uy, Jx, Jy);
             if constexpr (COLL == LBM_COLL_MRT)
-                collide_mrt<R>(g, rho, ux, uy, Fx, Fy, P);
+                collide_mrt<R>(g, rho, ux, uy, Jx, Jy, Fx, Fy, P);
             else
                 collide<R>(g, ref_cur, rho, ux, uy, Jx, Jy, Fx, Fy, P);
             // encoded as a single step stores them: rounded to the storage
@@ -1351,7 +1456,7 @@ __device__ __forceinline__ void walk2(const typename Store<ST>::E *__restrict__ 
             R ux, uy, Jx, Jy;
             velocity<R>(g, rho, Fx, Fy, ux, uy, Jx, Jy);
             if constexpr (COLL == LBM_COLL_MRT)
-                collide_mrt<R>(g, rho, ux, uy, Fx, Fy, P);
+                collide_mrt<R>(g, rho, ux, uy, Jx, Jy, Fx, Fy, P);
             else
                 collide<R>(g, ref_cur, rho, ux, uy, Jx, Jy, Fx, Fy, P);
             const int sb = m - 6;
