@@ -128,11 +128,11 @@ struct Coeffs {
 };
 
 // The forms of the force, the velocity and the collisions with the fewest
-// operations, for FP64 (BGK: 114 FP64 instructions per cell and step where the
-// forms written next to them take 143; 2048 x 8192 cells 128 -> 119 us per
+// operations, for FP64 (BGK: 115 FP64 instructions per cell and step where the
+// forms written next to them take 143; 2048 x 8192 cells 128 -> 117 us per
 // step in the deep pass).  They round differently from those, by a few 1e-16
 // of the values; against the equations in 80 bits, over 24 lattices of 40 to
-// 110 cells a side and 20 to 120 steps, the populations are off by 3.5e-15
+// 110 cells a side and 20 to 120 steps, the populations are off by 9.4e-15
 // (BGK, rms; 9.3e-15 in the other forms) and 6.4e-15 (MRT; 6.3e-15).  The
 // modes that store rounded populations keep the other forms: there a last bit
 // decides which way a stored value rounds, so results would change by the
@@ -156,11 +156,9 @@ struct Phys {
     R m3g, om2;                       // -3 guo, omega/2 (collide)
     // collide_mrt: 1 - s and 1 - s/2 of each rate (n: omega, the stress rows)
     R ke, he, kz, hz, kq, hq, kn, hn;
-    // kFewerOps: force's weights of s0, s58, s13 and s24 with G0 in them,
-    // omega/9 and omega/36, 6 he, 6 hz and 2 hn.  keep is 1 - 9 (omega/9) with
-    // the rounded omega/9 there: the weights of d and rho in the collision sum
-    // to one, and the mass does not drift by omega/9's rounding.
-    R h_0, h_58, h_2, h_1, om9, om36, he6, hz6, hn2;
+    // kFewerOps: force's weights of s0, s58, s13 and s24 with G0 in them, 6 he,
+    // 6 hz and 2 hn
+    R h_0, h_58, h_2, h_1, he6, hz6, hn2;
     Phys() = default;
     __host__ __device__ explicit Phys(const Coeffs &c)
         : omega((R)c.omega), guo((R)c.guo), eos_b((R)c.eos_b), kcT((R)c.kcT), ka((R)c.ka),
@@ -173,13 +171,11 @@ struct Phys {
           t0((R)((c.cSC + c.cB * (c.trace_alt ? -10.0 / 27.0 : -8.0 / 27.0)) / 9.0)),
           t1((R)(c.cB * (c.trace_alt ? 2.0 / 27.0 : 1.0 / 27.0) / 9.0)),
           t2((R)(c.cB * (c.trace_alt ? 1.0 / 54.0 : 1.0 / 27.0) / 9.0)),
-          keep(kFewerOps<R> ? (R)fma(-9.0, c.omega / 9.0, 1.0) : (R)(1.0 - c.omega)),
-          om3((R)(c.omega / 3.0)), g3((R)(c.guo / 3.0)),
+          keep((R)(1.0 - c.omega)), om3((R)(c.omega / 3.0)), g3((R)(c.guo / 3.0)),
           m3g(R(-3) * guo), om2(R(0.5) * omega), ke(R(1) - s_e), he(R(1) - R(0.5) * s_e),
           kz(R(1) - s_z), hz(R(1) - R(0.5) * s_z), kq(R(1) - s_q), hq(R(1) - R(0.5) * s_q),
           kn(R(1) - omega), hn(R(1) - R(0.5) * omega), h_0(t0 + m2_0), h_58(t2 + m2_58),
-          h_2(t1 + m2_2), h_1(t1 + m2_1), om9((R)(c.omega / 9.0)), om36((R)(c.omega / 36.0)),
-          he6(R(6) * he), hz6(R(6) * hz), hn2(R(2) * hn)
+          h_2(t1 + m2_2), h_1(t1 + m2_1), he6(R(6) * he), hz6(R(6) * hz), hn2(R(2) * hn)
     {
     }
 };
@@ -477,8 +473,9 @@ __device__ __forceinline__ void velocity(const R d[kQ], R rho, R Fx, R Fy, R &ux
 //
 // With q = (omega/2) J + g F the axis terms are w (c.u)(h c.u + m c.F) = c.u c.q
 // = u_x q_x or u_y q_y, and with S = u_x q_x + u_y q_y the isotropic part is
-// w A = omega rho/9 - S/3, the diagonal pairs' T = omega rho/36 + S/6 +-
-// (u_x q_y + u_y q_x)/4: 17 operations less (kFewerOps).
+// w A = (omega rho - 3 S)/9, the diagonal pairs' T = (w A + S +- (u_x q_y +
+// u_y q_x))/4: 16 operations less (kFewerOps).  Where u = F = 0 each form
+// rounds like the other.
 template <class R>
 __device__ __forceinline__ void collide(R d[kQ], R ref, R rho, R ux, R uy, R Jx, R Jy, R Fx,
                                         R Fy, const Phys<R> &P)
@@ -490,12 +487,12 @@ __device__ __forceinline__ void collide(R d[kQ], R ref, R rho, R ux, R uy, R Jx,
         const R Bx = fma(om, Jx, gx), By = fma(om, Jy, gy);  // B/3
         const R Ex = ux * qx, Ey = uy * qy, S = Ex + Ey;
         const R cross = fma(ux, qy, uy * qx);
-        const R A1 = fma(R(-1.0 / 3.0), S, P.om9 * rho);
-        const R W = fma(R(1.0 / 6.0), S, P.om36 * rho);
+        const R A1 = R(1.0 / 9.0) * fma(R(-3), S, om * rho);
+        const R W = R(0.25) * (A1 + S);
         const R Tx = Ex + A1, Ty = Ey + A1;
         const R T5 = fma(R(0.25), cross, W), T6 = fma(R(-0.25), cross, W);
         const R B5 = Bx + By, B6 = By - Bx;
-        d[0] = fma(R(4), A1, keep * d[0]);
+        d[0] = fma(keep, d[0], R(4) * A1);
         d[1] = fma(keep, d[1], fma(R(1.0 / 3.0), Bx, Tx));
         d[3] = fma(keep, d[3], fma(R(-1.0 / 3.0), Bx, Tx));
         d[2] = fma(keep, d[2], fma(R(1.0 / 3.0), By, Ty));
