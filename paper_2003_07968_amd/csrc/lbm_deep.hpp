@@ -286,15 +286,15 @@ __device__ __forceinline__ void deep_stage(
 #pragma unroll
                 for (int i = 0; i < kQ; ++i) {
                     const R wt = i == 0 ? R(4.0 / 9.0) : (i < 5 ? R(1.0 / 9.0) : R(1.0 / 36.0));
-                    const R dev = fma(-wt, sd, h[i]);
-                    X[i] = (E)dev;
-                    err += dev - (R)X[i];
+                    h[i] = fma(-wt, sd, h[i]);
                 }
-                newref = (float)(ref + (sd + err));
-            } else {
+                to_stored<E, R>(h, X);
 #pragma unroll
                 for (int i = 0; i < kQ; ++i)
-                    X[i] = (E)h[i];
+                    err += h[i] - (R)X[i];
+                newref = (float)(ref + (sd + err));
+            } else {
+                to_stored<E, R>(h, X);
             }
             if constexpr (ROLE == kLast) {
                 if (interior && a >= 2 && a < n + 2) {

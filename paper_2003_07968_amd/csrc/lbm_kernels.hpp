@@ -633,6 +633,28 @@ __device__ __forceinline__ double weight(int i)
     return i == 0 ? 4.0 / 9.0 : (i < 5 ? 1.0 / 9.0 : 1.0 / 36.0);
 }
 
+// The stored values of nine populations.  binary16 is rounded to two at a
+// time (v_cvt_pk_f16_f32: five instructions, not nine).
+template <class E, class R>
+__device__ __forceinline__ void to_stored(const R d[kQ], E X[kQ])
+{
+    if constexpr (std::is_same_v<E, _Float16>) {
+        typedef float F2 __attribute__((ext_vector_type(2)));
+        typedef _Float16 H2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int i = 0; i < kQ - 1; i += 2) {
+            const H2 h = __builtin_convertvector((F2{d[i], d[i + 1]}), H2);
+            X[i] = h.x;
+            X[i + 1] = h.y;
+        }
+        X[kQ - 1] = (E)d[kQ - 1];
+    } else {
+#pragma unroll
+        for (int i = 0; i < kQ; ++i)
+            X[i] = (E)d[i];
+    }
+}
+
 // Equilibrium (Eq. SEDF) of direction i, FP64.
 __device__ __forceinline__ double feq_dir(int i, double rho, double ux, double uy)
 {
