@@ -6,12 +6,13 @@ of the Carnahan-Starling EOS (a=1, b=4, R=1 convention) at reduced
 temperatures 0.6, 0.7, 0.8 and 0.9, BGK tau = 1, G = -1, eps = 1.73, sigma = 1.
 One bench step advances each of the four lattices by one time step.  The
 four lattices form one batch (the library's batch entry points), so one
-kernel launch covers all four, and the library takes two time steps per
-launch (the two-step pass: read the populations once, compute both steps,
-write once); an odd step count ends with one single-step launch.  The
-launch shape is fixed per storage mode (SLAB_LAUNCH, the fastest of launch
-sweeps of this workload); --launch sets another, --autotune lets the
-library's batch autotuner pick one.
+kernel launch covers all four, and the library takes four time steps per
+launch (the deep pass: read the populations once, compute four steps, write
+once), in the shape that it chooses; what is left of the step count goes
+through the two-step pass and the single step.  --fusion 2 and 1 measure those
+two alone, in a fixed launch shape per storage mode (SLAB_LAUNCH, the fastest
+of launch sweeps of this workload); --launch sets another two-step shape,
+--autotune lets the library's batch autotuner pick form and shape.
 --one-by-one gives each lattice launches of its own instead; the default line
 carries that rate too (`one_lattice_per_launch`).  Inputs are resident in HBM
 before timing.
@@ -23,15 +24,17 @@ the timed region; every step, warm-up included, is checked for a sticky
 domain error after the timed region.
 
 Output: one JSON line.  `value` is lattice updates per second over the timed
-steps (MLUPS).  `roofline` prices the dominant kernel (the batched two-step
-pass; the batched single step with --fusion 1) at the algorithmic bytes of a
-cell update, one read and one write of its populations (144 B in FP64,
-72 / 36 / 44 B in the reduced-precision modes), times the updates one launch
-makes (two per cell of the four lattices for the two-step pass), over its
+steps (MLUPS).  `roofline` prices the dominant kernel (the batched deep
+pass; the two-step pass or the single step with --fusion) at the algorithmic
+bytes of a cell update, one read and one write of its populations (144 B in
+FP64, 72 / 36 / 44 B in the reduced-precision modes), times the updates one
+launch makes (four per cell of the four lattices for the deep pass), over its
 average launch duration timed with HIP events on the library's stream,
-against the 8 TB/s HBM peak.  Because a
-two-step launch reads and writes the populations once for two updates, that
-fraction can exceed 1; `roofline.per_launch_hbm` gives the launch's own
+against the 8 TB/s HBM peak.  Because a launch of several steps reads and
+writes the populations once for all of them, that fraction can exceed 1;
+`roofline.valu` has the launch's VALU instructions against one per four cycles
+of every SIMD (some issue faster: it can exceed 1 too) while there is a
+current counter record.  `roofline.per_launch_hbm` gives the launch's own
 bytes (one read and one write per cell) against the peak, against a plain
 device copy measured in the same run, and (FP64) against the stream probe: the
 same population access pattern without the arithmetic (lbm_probe_stream).  `traffic` is the counter-measured HBM
@@ -81,12 +84,14 @@ HBM_PEAK_GBS = 8000.0         # MI355X HBM3E
 VALU_PEAK_GIPS = 614.4
 # storage modes whose two-step pass is bound by VALU issue (committed counters)
 ISSUE_BOUND = ("f16", "f16l")
+# time steps that one launch of each kernel takes
+STEPS_PER_LAUNCH = {"deep": 4, "pass2": 2, "step": 1}
 METRIC = "MLUPS/GPU and % HBM roofline (FP64 vs FP32/FP16-shifted); p50/p99 time-to-result"
 N = 2048
 TEMPS = (0.6, 0.7, 0.8, 0.9)
 WARMUP_FLOOR_STEPS = 200      # untimed steps before any timed region
-# Launch shape (threads per workgroup, segment rows) of the four-lattice batch
-# per steps per launch and storage mode: the fastest of `--launch` sweeps of
+# Launch shape of the two-step pass and the single step (--fusion; threads per
+# workgroup, segment rows) of the four-lattice batch per steps per launch and storage mode: the fastest of `--launch` sweeps of
 # this workload (two-step pass, G cell updates/s: FP64 rows 24/32/37/48 gave
 # 71.2/72.7/71.8/66.9; FP32 rows 12/16/21 137.2/136.6/136.1, within run-to-run
 # noise; FP16 rows 24/30/37/48 176.7/181.5/185.1/169.1; per-cell FP16 the same
@@ -97,17 +102,28 @@ WARMUP_FLOOR_STEPS = 200      # untimed steps before any timed region
 SLAB_LAUNCH = {2: {"f64": (256, 32), "f32": (256, 16), "f16": (256, 37), "f16l": (256, 37)},
                1: {"f64": (256, 5), "f32": (256, 5), "f16": (256, 5), "f16l": (256, 5)}}
 PRECISION_STEPS = 400         # timed steps per reduced-precision mode
-KERNEL_SRC = os.path.join(ROOT, "paper_2003_07968_amd", "csrc", "lbm_kernels.hpp")
+KERNEL_SRC = [os.path.join(ROOT, "paper_2003_07968_amd", "csrc", name)
+              for name in ("lbm_kernels.hpp", "lbm_deep.hpp")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_{kernel}_{storage}_4x2048.json")
 DTYPE = {"f64": "f64", "f32": "f32 (FP32-shifted storage)",
          "f16": "f32 arithmetic, f16-shifted storage",
          "f16l": "f32 arithmetic, f16 storage with per-cell f32 reference"}
 # What limits each dominant kernel, from the committed counter profiles
-# (profiles/pass2_4x2048_sq_counters.md, profiles/pass2_*_4x2048_traffic.md):
+# (profiles/deep_4x2048_counters.md, profiles/pass2_4x2048_sq_counters.md, profiles/pass2_*_4x2048_traffic.md):
 # counter-measured HBM bytes against a plain device copy, and VALU issue time
 # (SQ_INSTS_VALU x 4 cycles per wave64 instruction over 1024 SIMDs at 2.4 GHz)
 # against the launch time.
 LIMITER = {
+    ("deep", "f64"): "hbm and latency: 1.02x the algorithmic bytes at 5.2 TB/s, a plain device "
+                     "copy's rate; VALU issue 51% of the launch (63% at the 1.96 GHz that FP64 "
+                     "arithmetic holds), 28% of wave-cycles waiting at four waves per SIMD "
+                     "(profiles/deep_4x2048_counters.md)",
+    ("deep", "f32"): "valu: FP32 arithmetic issue 94% of the launch; HBM 4.4 TB/s, 1.03x the "
+                     "algorithmic bytes (profiles/deep_4x2048_counters.md)",
+    ("deep", "f16"): "valu: more than one FP32 instruction per four cycles of every SIMD; HBM "
+                     "2.4 TB/s, 1.05x the algorithmic bytes (profiles/deep_4x2048_counters.md)",
+    ("deep", "f16l"): "valu: more than one FP32 instruction per four cycles of every SIMD; HBM "
+                      "2.1 TB/s, 1.05x the algorithmic bytes (profiles/deep_4x2048_counters.md)",
     ("pass2", "f64"): "hbm and latency: 1.06x the algorithmic bytes at about 5.5 TB/s, above a "
                       "plain device copy's rate and about 95% of the stream probe of the same "
                       "access pattern (roofline.per_launch_hbm.stream_probe_gbs); "
@@ -129,12 +145,15 @@ def err(msg):
 
 
 def source_digest():
-    with open(KERNEL_SRC, "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in KERNEL_SRC:
+        with open(name, "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()[:16]
 
 
 def counter_record(kernel, storage, shape=None):
-    """The committed rocprofv3 counter record of `kernel` ("pass2" or "step")
+    """The committed rocprofv3 counter record of `kernel` (a key of STEPS_PER_LAUNCH)
     in this storage mode, if it was taken on the current kernel source and,
     when `shape` (block_x, seg_rows) is given, at that launch shape (the
     traffic of a launch depends on its segments' halo rows)."""
@@ -285,12 +304,10 @@ def cpu_baseline(runs=3, steps_one=2, steps_all=6):
 def run_batch(args):
     """256 independent droplet lattices (sides log-uniform in [64, 512], T_r
     U[0.55, 0.95], sigma U[1/8, 4], R0 U[0.15, 0.35] side, seed 6) stepped by
-    one batched launch per two steps (the two-step pass) or per step, as the
-    autotuner finds faster (--fusion 1: single steps only), with FP32-shifted
-    storage, shape chosen by the autotuner,
-    8-step HIP graphs replayed.  Beside it, the same lattices in FP64 stepped
-    each on its own (the plain path: one two-step launch per lattice per two
-    steps)."""
+    one batched launch per four steps, two or one, as the autotuner finds
+    fastest (--fusion 1: single steps only, replayed as 8-step HIP graphs), with
+    FP32-shifted storage.  Beside it, the same lattices in FP64 stepped each on
+    its own (the plain path: one launch per lattice per two steps)."""
     import torch
     from paper_2003_07968_amd import lbm
     from paper_2003_07968_amd import workloads as W
@@ -349,9 +366,7 @@ def run_batch(args):
     plain_mlups = cells * seq_steps / (plain_ms / 1e3) / 1e6
     bpc = BYTES_PER_UPDATE[storage]
     step_ms = gpu_ms / args.steps
-    launches = args.steps // fusion + args.steps % fusion
-    launch_ms = gpu_ms / launches
-    achieved = bpc * cells / (launch_ms / 1e3) / 1e9
+    achieved = bpc * cells / (step_ms / 1e3) / 1e9   # one read and write per update
     out = {
         "metric": METRIC, "value": round(mlups, 1), "unit": "MLUPS", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(step_ms, 5),
@@ -363,18 +378,18 @@ def run_batch(args):
         "config": {
             "workload": "batch of 256 D2Q9 droplet lattices, sides log-uniform [64, 512], "
                         "T_r U[0.55,0.95], sigma U[1/8,4], R0 U[0.15,0.35] side, seed 6; "
-                        f"one batched launch per {fusion} step(s), 8-step HIP "
-                        "graphs, autotuned shape",
+                        "batched launches, autotuned form and shape",
             "storage": storage, "lattices": len(lats), "cells": cells,
-            "steps_per_launch": fusion, "bytes_per_cell_and_launch": bpc,
-            "launch_block_x_seg_rows": [bx, rows],
+            "steps_per_launch": 1 if fusion == 1 else "4 or 2 (autotuned)",
+            "bytes_per_cell_update": bpc,
         },
         "roofline": {
             "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
-            "kernel": ("batch2_kernel (two steps per launch)" if fusion == 2 else
-                       "batch_step_kernel (one step per launch)"),
-            "kernel_avg_ms": round(launch_ms, 5),
+            "kernel": ("batch_step_kernel (one step per launch)" if fusion == 1 else
+                       "batch_deep_kernel or batch_block_kernel (four steps per launch), "
+                       "or batch2_kernel (two)"),
+            "kernel_avg_ms": None,
         },
         "plain_fp64_sequential": {
             "value": round(plain_mlups, 1), "unit": "MLUPS", "steps": seq_steps,
@@ -533,13 +548,13 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
              autotune=False):
     """The four-temperature 2048^2 slab workload in one storage mode.  The four
     lattices are advanced together through the library's batch entry points
-    (one launch covers all four lattices, two time steps per launch), with
-    the launch shape `shape` (block_x, seg_rows), by default SLAB_LAUNCH's,
-    or the one the batch autotuner picks; with one_by_one each lattice gets
-    launches of its own instead.  Untimed warm-up (at least
+    (one launch covers all four lattices and four time steps), or with
+    `fusion` steps per launch in the launch shape `shape` (block_x, seg_rows),
+    by default SLAB_LAUNCH's, or as the batch autotuner picks; with one_by_one
+    each lattice gets launches of its own instead.  Untimed warm-up (at least
     WARMUP_FLOOR_STEPS steps), then `steps` timed steps enqueued right behind
     it, bracketed by events on the library's stream, with events at about
-    every tenth of the paired steps for the spread.  Every lattice's sticky
+    every tenth of the whole launches for the spread.  Every lattice's sticky
     error word is checked after the timed region (it covers the warm-up
     too)."""
     import torch
@@ -547,6 +562,7 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
     from paper_2003_07968_amd import workloads as W
 
     stream = torch.cuda.Stream()  # graphs of the batch cannot be captured on the null stream
+    deep = fusion is None and shape is None   # the library's own choice
     with torch.cuda.stream(stream):
         lats = []
         for tr in TEMPS:
@@ -555,7 +571,9 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
             p["rho_ref"] = W.shift_reference(rho0, storage)
             p["collision"] = W.COLLISION[collision]
             lats.append(lbm.Lattice(p, rho0))
-            if fusion is not None:
+            if fusion == 2:
+                lats[-1].set_fusion(2, 256)   # a shape that is set holds for all steps
+            elif fusion is not None:
                 lats[-1].set_fusion(fusion)
         if one_by_one:
             batch = None
@@ -569,78 +587,77 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
                 batch.add(lat)
             if autotune:
                 batch.autotune()
-            else:
+            elif not deep:
                 batch.set_launch(fusion or 2, *(shape or SLAB_LAUNCH[fusion or 2][storage]))
             fus, bx, rows = batch.launch()
             launch = [bx, rows]
         torch.cuda.synchronize()
-        err(f"{storage}: lattices ready, {fus} step(s) per launch, "
+        kernel = "deep" if deep else ("pass2" if fus == 2 else "step")
+        per = STEPS_PER_LAUNCH[kernel]
+        if deep:
+            launch = None
+        err(f"{storage}: lattices ready, {per} step(s) per launch, "
             f"{'one lattice per launch' if one_by_one else 'four lattices per launch'}, "
-            f"launch shape {launch}")
+            f"launch shape {launch or 'chosen by the library'}")
 
         def advance(nsteps):
             if batch is not None:
                 batch.step(nsteps)
                 return
-            for _ in range(nsteps // 2):
+            for n in [per] * (nsteps // per) + [1] * (nsteps % per):
                 for lat in lats:
-                    lat.step(2)
-            for _ in range(nsteps % 2):
-                for lat in lats:
-                    lat.step(1)
+                    lat.step(n)
 
         e0 = torch.cuda.Event(enable_timing=True)
         em = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)
-        pairs, odd = divmod(steps, 2)
-        blk = max(1, pairs // 10)
+        groups, rest = divmod(steps, per)
+        blk = max(1, groups // 10)
         marks = []
         wsteps = max(warmup, WARMUP_FLOOR_STEPS)
-        wsteps += wsteps % 2          # whole pairs, so the timed region starts on a pair
+        wsteps += -wsteps % per       # whole launches before the timed region
         t0 = time.perf_counter()
         advance(wsteps)
         e0.record(stream)
-        done_pairs = 0
-        while done_pairs < pairs:
-            n = min(blk, pairs - done_pairs)
-            advance(2 * n)
-            done_pairs += n
+        done = 0
+        while done < groups:
+            n = min(blk, groups - done)
+            advance(per * n)
+            done += n
             ev = torch.cuda.Event(enable_timing=True)
             ev.record(stream)
             marks.append((n, ev))
         em.record(stream)
-        advance(odd)
+        advance(rest)
         e1.record(stream)
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
         for lat in lats:
             lat.sync()   # raises on a sticky domain error (warm-up or timed steps)
     gpu_ms = e0.elapsed_time(e1)
-    pair_ms = e0.elapsed_time(em)
+    group_ms = e0.elapsed_time(em)
     block_rates, prev = [], e0
     for n, ev in marks:
         ms = prev.elapsed_time(ev)
         if ms > 0:
-            block_rates.append(N * N * len(lats) * 2 * n / (ms / 1e3) / 1e6)
+            block_rates.append(N * N * len(lats) * per * n / (ms / 1e3) / 1e6)
         prev = ev
     err(f"{storage}: {wsteps} warm-up steps, then {steps} timed steps: {gpu_ms:.2f} ms on the "
         f"stream ({wall * 1e3:.1f} ms wall including the warm-up)")
-    # lattices one launch covers, and launches per pair of steps
+    # lattices one launch covers, and launches that advance all of them
     per_launch = 1 if one_by_one else len(lats)
-    launches_per_pair = len(lats) // per_launch * (1 if fus == 2 else 2)
-    if fus == 2 and pairs > 0:
-        kernel, launch_ms = "pass2", pair_ms / (pairs * launches_per_pair)
-        kname = ("sweep2_kernel (two steps per launch" if one_by_one else
-                 "batch2_kernel (two steps per launch, four lattices per launch")
-    else:
-        kernel = "step"
-        launch_ms = gpu_ms / (steps * len(lats) // per_launch)
-        kname = ("sweep_kernel (one step per launch" if one_by_one else
-                 "batch_step_kernel (one step per launch, four lattices per launch")
-    timed_launches = (pairs * launches_per_pair + odd * len(lats) // per_launch
-                      if fus == 2 else steps * len(lats) // per_launch)
+    launches = len(lats) // per_launch
+    launch_ms = (group_ms / (groups * launches) if groups > 0 else
+                 gpu_ms / (steps * launches))
+    name = {"deep": ("deep_kernel", "batch_deep_kernel"), "pass2": ("sweep2_kernel", "batch2_kernel"),
+            "step": ("sweep_kernel", "batch_step_kernel")}[kernel][0 if one_by_one else 1]
+    kname = (f"{name} ({('one step', 'two steps', None, 'four steps')[per - 1]} per launch" +
+             ("" if one_by_one else ", four lattices per launch"))
+    # what is left of a batched deep run: a two-step launch, a single step
+    tail = rest // 2 + rest % 2 if not one_by_one else rest
+    timed_launches = (groups + tail) * launches
     res = {"mlups": N * N * len(lats) * steps / (gpu_ms / 1e3) / 1e6, "gpu_ms": gpu_ms,
-           "launch_ms": launch_ms, "kernel": kernel, "kernel_name": kname, "fusion": fus,
+           "launch_ms": launch_ms, "kernel": kernel, "kernel_name": kname, "fusion": per,
            "launch": launch, "lattices": len(lats), "lattices_per_launch": per_launch,
            "timed_launches": timed_launches, "warmup_steps": wsteps,
            "block_rates": block_rates if len(block_rates) >= 5 else []}
@@ -651,15 +668,14 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
 
 def one_by_one_rate(batched_mlups, steps=PRECISION_STEPS):
     """The default workload with launches of one lattice each (the
-    single-lattice two-step kernel, four launches per pair of steps), beside
-    the batched figure of the line."""
+    single-lattice deep pass, four launches per four steps), beside the batched
+    figure of the line."""
     r = run_slab("f64", "bgk", None, steps, 0, one_by_one=True)
-    upl = 2 if r["kernel"] == "pass2" else 1
+    upl = STEPS_PER_LAUNCH[r["kernel"]]
     achieved = BYTES_PER_UPDATE["f64"] * upl * N * N / (r["launch_ms"] / 1e3) / 1e9
     return {"value": round(r["mlups"], 1), "unit": "MLUPS", "steps": steps,
             "kernel": r["kernel_name"] + ", f64 storage, bgk)",
             "kernel_avg_ms": round(r["launch_ms"], 5),
-            "launch_block_x_seg_rows_workgroups": list(r["launch"]),
             "roofline_frac": round(achieved / HBM_PEAK_GBS, 4),
             "batched_over_one_by_one": round(batched_mlups / r["mlups"], 3)}
 
@@ -671,18 +687,17 @@ def precision_rates(f64_mlups):
     out = {"steps": PRECISION_STEPS}
     for st in ("f32", "f16", "f16l"):
         r = run_slab(st, "bgk", None, PRECISION_STEPS, 0)
-        upl = 2 if r["kernel"] == "pass2" else 1
+        upl = STEPS_PER_LAUNCH[r["kernel"]]
         bpu = BYTES_PER_UPDATE[st]
         achieved = bpu * upl * N * N * r["lattices_per_launch"] / (r["launch_ms"] / 1e3) / 1e9
         out[st] = {"value": round(r["mlups"], 1), "unit": "MLUPS",
                    "speedup_vs_f64": round(r["mlups"] / f64_mlups, 3),
                    "bytes_per_cell_update": bpu, "steps_per_launch": r["fusion"],
                    "lattices_per_launch": r["lattices_per_launch"],
-                   "launch_block_x_seg_rows": list(r["launch"][:2]),
                    "kernel_avg_ms": round(r["launch_ms"], 5),
                    "roofline_frac": round(achieved / HBM_PEAK_GBS, 4),
                    "per_launch_hbm_frac": round(achieved / upl / HBM_PEAK_GBS, 4),
-                   "valu": valu_roofline(r["kernel"], st, r["launch_ms"], r["launch"][:2]),
+                   "valu": valu_roofline(r["kernel"], st, r["launch_ms"]),
                    "limiter": LIMITER.get((r["kernel"], st))}
     return out
 
@@ -737,18 +752,19 @@ def main():
     n_lat = res["lattices"]
     bpu = BYTES_PER_UPDATE[args.storage]
     kernel = res["kernel"]
-    upl = 2 if kernel == "pass2" else 1
+    upl = STEPS_PER_LAUNCH[kernel]
+    shape_used = res["launch"][:2] if res["launch"] else None
     launch_s = res["launch_ms"] / 1e3
     cells = N * N * res["lattices_per_launch"]   # cells one launch covers
     # the roofline of one cell update: one read and one write of its
-    # populations (bpu bytes) at peak bandwidth; a two-step launch makes two
-    # updates per cell with one read and one write, so its update rate can
-    # exceed that figure
+    # populations (bpu bytes) at peak bandwidth; a launch of several steps makes
+    # that many updates per cell with one read and one write, so its update
+    # rate can exceed that figure
     achieved = bpu * upl * cells / launch_s / 1e9
     launch_gbs = bpu * cells / launch_s / 1e9
     # the committed counter records are of the batched launch
     counters = args.collision == "bgk" and not args.one_by_one
-    traffic = measured_traffic(kernel, args.storage, res["launch"][:2]) if counters else None
+    traffic = measured_traffic(kernel, args.storage, shape_used) if counters else None
     copy_gbs = copy_bandwidth_gbs()
     probe_gbs = stream_probe_gbs() if args.storage == "f64" else None
     mlups = res["mlups"]
@@ -775,9 +791,9 @@ def main():
             "steps_per_launch": res["fusion"],
             "lattices_per_launch": res["lattices_per_launch"],
             "bytes_per_cell_update": bpu,
-            "launch_block_x_seg_rows": list(res["launch"][:2]),
-            "launch_from": ("each lattice's default" if args.one_by_one else
-                            "batch autotuner" if args.autotune else
+            "launch_block_x_seg_rows": list(shape_used) if shape_used else None,
+            "launch_from": ("batch autotuner" if args.autotune else
+                            "library default" if kernel == "deep" or args.one_by_one else
                             "--launch" if shape else "bench table (SLAB_LAUNCH)"),
             "timed_launches": res["timed_launches"],
             "untimed_warmup_steps": res["warmup_steps"],
@@ -793,7 +809,7 @@ def main():
             "kernel_avg_ms": round(res["launch_ms"], 5),
             "updates_per_launch_per_cell": upl,
             "limiter": LIMITER.get((kernel, args.storage)) if counters else None,
-            "valu": (valu_roofline(kernel, args.storage, res["launch_ms"], res["launch"][:2])
+            "valu": (valu_roofline(kernel, args.storage, res["launch_ms"], shape_used)
                      if counters else None),
             "per_launch_hbm": {
                 "bytes": bpu * cells,
@@ -806,10 +822,10 @@ def main():
             },
         },
     }
-    # the issue-bound modes (FP16 storage, FP32 arithmetic) are priced against
-    # the VALU issue rate, the HBM figures kept beside it
+    # the issue-bound two-step modes (FP16 storage, FP32 arithmetic) are priced
+    # against the VALU issue rate, the HBM figures kept beside it
     rf = out["roofline"]
-    if args.storage in ISSUE_BOUND and rf["valu"] is not None:
+    if kernel != "deep" and args.storage in ISSUE_BOUND and rf["valu"] is not None:
         v = rf.pop("valu")
         rf["hbm"] = {k: rf[k] for k in ("achieved", "peak", "unit", "frac")}
         rf.update(bound="alu", achieved=v["achieved"], peak=v["peak"], unit=v["unit"],

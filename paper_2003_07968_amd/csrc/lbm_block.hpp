@@ -13,9 +13,9 @@
 // neighbouring workgroups, on compute units that would be idle.
 //
 // What bounds it: latency.  A step is two barriers, two LDS exchanges and one
-// dependent chain of about 150 instructions, 0.7 us (FP32) to 0.95 us (FP64,
+// dependent chain of about 120 instructions, 0.7 us (FP32) to 0.95 us (FP64,
 // eight waves), and a launch costs 2 to 3 us besides.  us per step before
-// (the deep pass) and after: FP64 64^2 4.0 -> 1.7, 200^2 4.5 -> 2.1, 517 x 301
+// (the deep pass) and after: FP64 64^2 4.0 -> 1.6, 200^2 4.5 -> 2.1, 517 x 301
 // 6.1 -> 4.5; FP32 64^2 3.9 -> 1.5, 200^2 4.0 -> 1.6, 512^2 5.6 -> 4.7.  On larger
 // lattices the cells computed more than once (1.9 to 6 times as many) cost
 // more than the deep pass's start and end; four_shape in the host runtime

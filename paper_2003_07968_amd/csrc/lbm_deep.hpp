@@ -34,13 +34,15 @@
 // halo columns and rows on each side, and n rows take n + 6T - 3 iterations.
 //
 // What bounds it (T = 4, 2048 x 8192, one MI355X; the two-step pass on the
-// same lattice in parentheses): FP64 131 G cell updates/s (73), FP32 243
-// (134), FP16 254 (186), per-cell FP16 175 (148).  VALU issue: a row update
-// is 148 FP64 or 128 FP32 instructions per wave.  FP64 with 16 waves per CU
-// takes about 2900 cycles per iteration against 2512 of issue, at a clock
-// that FP64 arithmetic on all CUs holds at 1.8 - 2.0 GHz; FP32 and FP16, with
-// 32 waves, are at their issue rate.  HBM traffic is 1.02 times one read and
-// one write of the populations per launch, 4.7 TB/s in FP64.
+// same lattice in parentheses): FP64 143 G cell updates/s (73), FP32 248
+// (134), FP16 260 (186), per-cell FP16 185 (148).  A row update is 120
+// (FP64), 125 (FP32), 139 (FP16) or 192 (per-cell) VALU instructions per wave.
+// FP32 and the FP16 modes are at their issue rate (0.94 to 1.1 of one
+// instruction per four cycles of every SIMD at 2.4 GHz).  FP64, with 16 waves
+// per CU, issues at 0.51 of it, at a clock that FP64 arithmetic on all CUs
+// holds at 1.96 GHz, and waits 28% of its wave-cycles; its HBM traffic, 1.02
+// times one read and one write of the populations per launch, runs at 5.2
+// TB/s, a plain copy's rate.
 //
 // What the issue rate needed, each measured on that lattice in FP64:
 //   LDS addressed by byte offset from four registers (the compiler kept an

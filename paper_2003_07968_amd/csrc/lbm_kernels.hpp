@@ -18,7 +18,7 @@
 // from w_i R(z) with a per-cell FP32 reference R (the nine values a cell sends
 // share its R).  The diagnostics reductions are FP64 in every mode.
 //
-// Kernel design (one fused pass per step, or per two steps):
+// Kernel design (one fused pass per step, per two steps or per four):
 //   * populations are arrays X_i[y][x] holding the post-collision values of
 //     the previous step; the pulled value is f_i(x) = X_i(x - c_i), so every
 //     row is read with unit stride (shifted by at most one element) and
@@ -37,10 +37,13 @@
 //     which are re-read through L2; neighbouring segments walk in opposite
 //     directions, so both workgroups of a segment boundary touch its rows at
 //     about the same time;
-//   * two steps per pass (the default): the first step is computed on a tile
-//     widened by three columns and rows on each side and handed to the
-//     second through LDS, so the populations are read and written once per
-//     two updates (walk2 below);
+//   * two steps per pass: the first step is computed on a tile widened by
+//     three columns and rows on each side and handed to the second through
+//     LDS, so the populations are read and written once per two updates
+//     (walk2 below);
+//   * four steps per pass (the default for every whole group of four steps):
+//     the deep pass (lbm_deep.hpp), or on small lattices the block pass
+//     (lbm_block.hpp), which takes the remainder of a call too;
 //   * workgroups take their tiles in an XCD-aware order (xcd_tile).
 #include <hip/hip_runtime.h>
 
