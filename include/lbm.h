@@ -232,9 +232,9 @@ lbm_status lbm_set_launch(lbm_handle *h, int32_t block_x, int32_t seg_rows);
  * library's choice (256 threads; segments of 2..40 rows, as many as fill whole
  * rounds of the workgroups the device runs at once).  lbm_init selects 2.
  * With 2 and neither block_x nor seg_rows given, lbm_step may take more than
- * two steps per launch (four, in the deep pass or, on small lattices, the
- * block pass, which takes one to three at the end of a call as well); pairs
- * and an odd remainder follow in the forms above.  The results and the
+ * two steps per launch (four, or the last three of a call, in the deep pass
+ * or, on small lattices, the block pass, which takes the last one or two as
+ * well); a pair or a single step that is left follows in the forms above.  The results and the
  * first domain error are the same, bitwise.  A shape given here is used for
  * every pair of steps.
  * Batches have their own setting (lbm_batch_set_fusion). */

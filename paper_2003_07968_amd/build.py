@@ -39,7 +39,7 @@ FLAGS = [
 # (object name, source, extra defines)
 UNITS = [("lbm_host", "lbm.hip", [])] + [
     (f"lbm_st{st}_k{fam}", "lbm_inst.hip", [f"-DLBM_INST_ST={st}", f"-DLBM_INST_FAMILY={fam}"])
-    for fam in (3, 2, 1) for st in (0, 1, 2, 3)
+    for fam in (3, 4, 2, 1) for st in (0, 1, 2, 3)
 ] + [("server", "server.cpp", [])]
 
 # hipcc's host pass does not know the two GPU features and says so

@@ -703,7 +703,34 @@ hipError_t run_sweep2(lbm_handle *h, const void *src, void *dst)
     return hipErrorInvalidValue;
 }
 
-// kDeepSteps time steps in one pass, or 1 .. kDeepSteps in the block pass.
+// Whether a pass of `steps` steps is one launch of the form f: kDeepSteps steps
+// or one less, any number up to kDeepSteps in the block pass.  Three steps in
+// the deep pass, against a two-step launch and a single step, us: FP64 1024^2
+// 50 and 76, 2048^2 123 and 232; FP32 2048^2 76 and 128; FP16 69 and 91.  Two
+// steps are left to the two-step pass, which moves as many bytes for them as
+// the deep pass would.
+bool one_launch(const FourShape &f, int64_t steps)
+{
+    return f.block || steps >= kDeepSteps - 1;
+}
+
+template <int ST>
+hipError_t launch_long(const SweepArgs &a, bool block, int steps)
+{
+    return block                 ? launch_block<ST>(a, steps)
+           : steps == kDeepSteps ? launch_deep<ST, kDeepSteps>(a)
+                                 : launch_deep<ST, kDeepSteps - 1>(a);
+}
+
+template <int ST>
+hipError_t launch_batch_long(const BatchArgs &a, bool block, int steps)
+{
+    return block                 ? launch_batch_block<ST>(a, steps)
+           : steps == kDeepSteps ? launch_batch_deep<ST, kDeepSteps>(a)
+                                 : launch_batch_deep<ST, kDeepSteps - 1>(a);
+}
+
+// `steps` time steps (see one_launch) in one pass.
 hipError_t run_four(lbm_handle *h, const void *src, void *dst, int steps = kDeepSteps)
 {
     SweepArgs a = sweep_args(h, src, dst, Fields{}, true);
@@ -711,14 +738,10 @@ hipError_t run_four(lbm_handle *h, const void *src, void *dst, int steps = kDeep
     a.bx = h->shape4.bx;
     const bool block = h->shape4.block;
     switch (h->c.storage) {
-    case LBM_STORE_F64:
-        return block ? launch_block<LBM_STORE_F64>(a, steps) : launch_deep<LBM_STORE_F64>(a);
-    case LBM_STORE_F32_SHIFTED:
-        return block ? launch_block<LBM_STORE_F32_SHIFTED>(a, steps) : launch_deep<LBM_STORE_F32_SHIFTED>(a);
-    case LBM_STORE_F16_SHIFTED:
-        return block ? launch_block<LBM_STORE_F16_SHIFTED>(a, steps) : launch_deep<LBM_STORE_F16_SHIFTED>(a);
-    case LBM_STORE_F16_LOCAL:
-        return block ? launch_block<LBM_STORE_F16_LOCAL>(a, steps) : launch_deep<LBM_STORE_F16_LOCAL>(a);
+    case LBM_STORE_F64: return launch_long<LBM_STORE_F64>(a, block, steps);
+    case LBM_STORE_F32_SHIFTED: return launch_long<LBM_STORE_F32_SHIFTED>(a, block, steps);
+    case LBM_STORE_F16_SHIFTED: return launch_long<LBM_STORE_F16_SHIFTED>(a, block, steps);
+    case LBM_STORE_F16_LOCAL: return launch_long<LBM_STORE_F16_LOCAL>(a, block, steps);
     }
     return hipErrorInvalidValue;
 }
@@ -793,11 +816,11 @@ lbm_status read_sticky(lbm_handle *h)
 }
 
 
-// Whether a launch of `steps` steps is one of the long passes: kDeepSteps
-// steps, or 1 .. kDeepSteps in the block pass (as lbm_step takes them).
+// Whether a launch of `steps` steps is one of the long passes, as lbm_step
+// takes them.
 bool batch_long(const lbm_batch *b, int steps)
 {
-    return steps == kDeepSteps || (b->total_tiles4 > 0 && b->shape4.block);
+    return steps == kDeepSteps || (b->total_tiles4 > 0 && one_launch(b->shape4, steps));
 }
 
 BatchArgs batch_args(const lbm_batch *b, int steps, const long long *ctr, long long steps_add,
@@ -816,7 +839,7 @@ BatchArgs batch_args(const lbm_batch *b, int steps, const long long *ctr, long l
                      b->stream};
 }
 
-// One batched launch of `steps` (1, 2 or kDeepSteps) steps starting where batch_pos says:
+// One batched launch of `steps` (1, 2 or see batch_long) steps starting where batch_pos says:
 // eager launches pass the position (ctr = nullptr), captured ones their offset
 // from the device counters.
 hipError_t batch_launch_steps(lbm_batch *b, int steps, const long long *ctr, long long steps_add,
@@ -826,17 +849,10 @@ hipError_t batch_launch_steps(lbm_batch *b, int steps, const long long *ctr, lon
     if (batch_long(b, steps)) {
         const bool block = b->shape4.block;
         switch (b->storage) {
-        case LBM_STORE_F64:
-            return block ? launch_batch_block<LBM_STORE_F64>(a, steps) : launch_batch_deep<LBM_STORE_F64>(a);
-        case LBM_STORE_F32_SHIFTED:
-            return block ? launch_batch_block<LBM_STORE_F32_SHIFTED>(a, steps)
-                         : launch_batch_deep<LBM_STORE_F32_SHIFTED>(a);
-        case LBM_STORE_F16_SHIFTED:
-            return block ? launch_batch_block<LBM_STORE_F16_SHIFTED>(a, steps)
-                         : launch_batch_deep<LBM_STORE_F16_SHIFTED>(a);
-        case LBM_STORE_F16_LOCAL:
-            return block ? launch_batch_block<LBM_STORE_F16_LOCAL>(a, steps)
-                         : launch_batch_deep<LBM_STORE_F16_LOCAL>(a);
+        case LBM_STORE_F64: return launch_batch_long<LBM_STORE_F64>(a, block, steps);
+        case LBM_STORE_F32_SHIFTED: return launch_batch_long<LBM_STORE_F32_SHIFTED>(a, block, steps);
+        case LBM_STORE_F16_SHIFTED: return launch_batch_long<LBM_STORE_F16_SHIFTED>(a, block, steps);
+        case LBM_STORE_F16_LOCAL: return launch_batch_long<LBM_STORE_F16_LOCAL>(a, block, steps);
         }
         return hipErrorInvalidValue;
     }
@@ -1209,9 +1225,9 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps)
         while (h->four && k < nsteps) {
             // the block pass takes the remainder of a call too (64^2 FP64: 3.8,
             // 4.5 and 5.5 us for one to three steps, against 8, 10 and 18 in the
-            // other forms); the deep pass only whole groups
+            // other forms), the deep pass three steps
             const int n = (int)std::min<int64_t>(kDeepSteps, nsteps - k);
-            if (n < kDeepSteps && !h->shape4.block) break;
+            if (!one_launch(h->shape4, n)) break;
             hipError_t e = run_four(h, h->cur, h->nxt, n);
             if (e != hipSuccess) return dev_fail(h, e, "launching the four-step kernel");
             std::swap(h->cur, h->nxt);

@@ -30,6 +30,7 @@
 //   of the row itself belong to row w, those pulled from the previous row to
 //   row w + 1, and are held in registers until then;
 //   turns row a into rho and psi and publishes psi.
+// T is kDeepSteps, or one less for the three steps that a call may leave.
 // A step's lag is 4 rows behind the previous step's; a tile needs 2T - 1
 // halo columns and rows on each side, and n rows take n + 6T - 3 iterations.
 //
@@ -505,15 +506,14 @@ __global__ __launch_bounds__(BX *T, (kDeepWaves<ST>)) void batch_deep_kernel(con
 
 #define LBM_WIDTHSD(X) X(64) X(128) X(256)
 
-template <int ST, int COLL>
+template <int T, int ST, int COLL>
 hipError_t deep_launch_bx(const SweepArgs &a)
 {
     const dim3 grid((unsigned)a.tl.ntiles);
     switch (a.bx) {
 #define LBM_CASE(BX)                                                                          \
     case BX:                                                                                  \
-        hipLaunchKernelGGL((deep_kernel<BX, kDeepSteps, ST, COLL>), grid,                      \
-                           dim3(BX *kDeepSteps), 0, a.stream, a.src, a.dst, a.c,              \
+        hipLaunchKernelGGL((deep_kernel<BX, T, ST, COLL>), grid, dim3(BX *T), 0, a.stream, a.src, a.dst, a.c,              \
                            Phys<typename Store<ST>::R>(a.c), a.tl, a.t, a.err);                                                            \
         break;
         LBM_WIDTHSD(LBM_CASE)
@@ -524,21 +524,20 @@ hipError_t deep_launch_bx(const SweepArgs &a)
     return hipGetLastError();
 }
 
-template <int ST>
+template <int ST, int T>
 hipError_t launch_deep(const SweepArgs &a)
 {
-    return a.c.coll == LBM_COLL_MRT ? deep_launch_bx<ST, LBM_COLL_MRT>(a)
-                                    : deep_launch_bx<ST, LBM_COLL_BGK>(a);
+    return a.c.coll == LBM_COLL_MRT ? deep_launch_bx<T, ST, LBM_COLL_MRT>(a)
+                                    : deep_launch_bx<T, ST, LBM_COLL_BGK>(a);
 }
 
-template <int ST, int COLL>
+template <int T, int ST, int COLL>
 hipError_t batch_deep_launch_bx(const BatchArgs &a)
 {
     switch (a.bx) {
 #define LBM_CASE(BX)                                                                          \
     case BX:                                                                                  \
-        hipLaunchKernelGGL((batch_deep_kernel<BX, kDeepSteps, ST, COLL>), dim3(a.grid),        \
-                           dim3(BX *kDeepSteps), 0, a.stream, a.table, a.nlat, a.ctr,         \
+        hipLaunchKernelGGL((batch_deep_kernel<BX, T, ST, COLL>), dim3(a.grid), dim3(BX *T), 0, a.stream, a.table, a.nlat, a.ctr,         \
                            a.steps_add, a.launches_add);                                      \
         break;
         LBM_WIDTHSD(LBM_CASE)
@@ -549,11 +548,11 @@ hipError_t batch_deep_launch_bx(const BatchArgs &a)
     return hipGetLastError();
 }
 
-template <int ST>
+template <int ST, int T>
 hipError_t launch_batch_deep(const BatchArgs &a)
 {
-    return a.coll == LBM_COLL_MRT ? batch_deep_launch_bx<ST, LBM_COLL_MRT>(a)
-                                  : batch_deep_launch_bx<ST, LBM_COLL_BGK>(a);
+    return a.coll == LBM_COLL_MRT ? batch_deep_launch_bx<T, ST, LBM_COLL_MRT>(a)
+                                  : batch_deep_launch_bx<T, ST, LBM_COLL_BGK>(a);
 }
 
 }  // namespace lbmk

@@ -1903,23 +1903,27 @@ hipError_t launch_permute(const void *in, void *out, const Coeffs &c, int to_can
 #define LBM_DECLARE_FAMILY2(EXT, ST)                                                          \
     EXT template hipError_t launch_sweep2<ST>(const SweepArgs &);                             \
     EXT template hipError_t launch_batch2<ST>(const BatchArgs &);
-// Launchers of the deep pass (lbm_deep.hpp): kDeepSteps steps of one lattice
-// or of a batch in one launch, with the force.
+// Launchers of the deep pass (lbm_deep.hpp): T steps of one lattice or of a
+// batch in one launch, with the force; kDeepSteps, or one less for the
+// remainder of a call.
 constexpr int kDeepSteps = 4;
 constexpr int kHaloD = 2 * kDeepSteps - 1;  // halo columns and rows of a tile
 // Block pass: columns of a workgroup's region and of the cells it advances.
 constexpr int kBlockW = 32, kBlockCols = kBlockW - 2 * kHaloD;
-template <int ST> hipError_t launch_deep(const SweepArgs &a);
-template <int ST> hipError_t launch_batch_deep(const BatchArgs &a);
+template <int ST, int T> hipError_t launch_deep(const SweepArgs &a);
+template <int ST, int T> hipError_t launch_batch_deep(const BatchArgs &a);
 // Launchers of the block pass (lbm_block.hpp), likewise, for 1 .. kDeepSteps
 // steps.
 template <int ST> hipError_t launch_block(const SweepArgs &a, int steps);
 template <int ST> hipError_t launch_batch_block(const BatchArgs &a, int steps);
 #define LBM_DECLARE_FAMILY3(EXT, ST)                                                          \
-    EXT template hipError_t launch_deep<ST>(const SweepArgs &);                               \
-    EXT template hipError_t launch_batch_deep<ST>(const BatchArgs &);                         \
+    EXT template hipError_t launch_deep<ST, kDeepSteps>(const SweepArgs &);                   \
+    EXT template hipError_t launch_batch_deep<ST, kDeepSteps>(const BatchArgs &);             \
     EXT template hipError_t launch_block<ST>(const SweepArgs &, int);                         \
     EXT template hipError_t launch_batch_block<ST>(const BatchArgs &, int);
+#define LBM_DECLARE_FAMILY4(EXT, ST)                                                          \
+    EXT template hipError_t launch_deep<ST, kDeepSteps - 1>(const SweepArgs &);               \
+    EXT template hipError_t launch_batch_deep<ST, kDeepSteps - 1>(const BatchArgs &);
 #define LBM_EXTERN extern
 LBM_DECLARE_FAMILY1(LBM_EXTERN, LBM_STORE_F64)
 LBM_DECLARE_FAMILY1(LBM_EXTERN, LBM_STORE_F32_SHIFTED)
@@ -1933,6 +1937,10 @@ LBM_DECLARE_FAMILY3(LBM_EXTERN, LBM_STORE_F64)
 LBM_DECLARE_FAMILY3(LBM_EXTERN, LBM_STORE_F32_SHIFTED)
 LBM_DECLARE_FAMILY3(LBM_EXTERN, LBM_STORE_F16_SHIFTED)
 LBM_DECLARE_FAMILY3(LBM_EXTERN, LBM_STORE_F16_LOCAL)
+LBM_DECLARE_FAMILY4(LBM_EXTERN, LBM_STORE_F64)
+LBM_DECLARE_FAMILY4(LBM_EXTERN, LBM_STORE_F32_SHIFTED)
+LBM_DECLARE_FAMILY4(LBM_EXTERN, LBM_STORE_F16_SHIFTED)
+LBM_DECLARE_FAMILY4(LBM_EXTERN, LBM_STORE_F16_LOCAL)
 #undef LBM_EXTERN
 
 
