@@ -604,7 +604,7 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
             if batch is not None:
                 batch.step(nsteps)
                 return
-            for n in [per] * (nsteps // per) + [1] * (nsteps % per):
+            for n in [per] * (nsteps // per) + [nsteps % per] * (nsteps % per > 0):
                 for lat in lats:
                     lat.step(n)
 
@@ -653,9 +653,8 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
             "step": ("sweep_kernel", "batch_step_kernel")}[kernel][0 if one_by_one else 1]
     kname = (f"{name} ({('one step', 'two steps', None, 'four steps')[per - 1]} per launch" +
              ("" if one_by_one else ", four lattices per launch"))
-    # what is left of a batched deep run: a two-step launch, a single step
-    tail = rest // 2 + rest % 2 if not one_by_one else rest
-    timed_launches = (groups + tail) * launches
+    # what is left, one to three steps, is one launch too
+    timed_launches = (groups + (rest > 0)) * launches
     res = {"mlups": N * N * len(lats) * steps / (gpu_ms / 1e3) / 1e6, "gpu_ms": gpu_ms,
            "launch_ms": launch_ms, "kernel": kernel, "kernel_name": kname, "fusion": per,
            "launch": launch, "lattices": len(lats), "lattices_per_launch": per_launch,
