@@ -257,7 +257,8 @@ lbm_status lbm_get_launch(const lbm_handle *h, int32_t out[3]);
  * steps are timed at the library's shape and used while they are the fastest;
  * the shape reported is then the two-step pass's, for the steps they leave.
  * The timed launches write only the spare population buffer and are not
- * counted as steps, so the state and t are unchanged.  Synchronous; out (may be NULL) receives the
+ * counted as steps, so the state and t are unchanged; a domain error that they
+ * meet at t or later is not recorded.  Synchronous; out (may be NULL) receives the
  * chosen block_x, seg_rows and the measured microseconds per time step. */
 lbm_status lbm_autotune(lbm_handle *h, double out[3]);
 

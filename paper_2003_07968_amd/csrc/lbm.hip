@@ -12,6 +12,7 @@
 #include <atomic>
 #include <cstring>
 #include <mutex>
+#include <optional>
 #include <vector>
 
 using namespace lbmk;
@@ -119,6 +120,7 @@ struct lbm_handle {
     double *partials;        // per-tile diagnostics
     double *diag_out;        // kDiag doubles
     unsigned long long *err; // sticky domain-error key
+    unsigned long long *spare_err;  // where timed launches leave theirs (SpareErrors)
     int64_t t;
     int bx, seg_rows;
     Tiles tiles;
@@ -913,6 +915,23 @@ double time_launches(hipStream_t stream, int reps, Fn &&fn, int warm = 1)
     return us;
 }
 
+// While it lives, launches of these lattices report domain errors to their
+// spare words.  A timed launch checks the EOS at steps that are not taken, up
+// to kDeepSteps - 1 past t, and their errors are none of the lattice's.
+struct SpareErrors {
+    lbm_handle *const *h;
+    size_t n;
+    SpareErrors(lbm_handle *const *h_, size_t n_) : h(h_), n(n_) { exchange(); }
+    ~SpareErrors() { exchange(); }
+    SpareErrors(const SpareErrors &) = delete;
+    SpareErrors &operator=(const SpareErrors &) = delete;
+    void exchange()
+    {
+        for (size_t k = 0; k < n; ++k)
+            std::swap(h[k]->err, h[k]->spare_err);
+    }
+};
+
 // A launch shape and its timed duration per launch.
 struct Shape {
     double us;
@@ -1173,6 +1192,8 @@ lbm_status lbm_init(const lbm_params *params, void *d_workspace, size_t workspac
     char *ws = (char *)d_workspace;
     h->err = (unsigned long long *)(ws + L.err);
     h->diag_out = (double *)(ws + L.diag_out);
+    static_assert((kDiag + 1) * sizeof(double) <= kAlign);
+    h->spare_err = (unsigned long long *)(h->diag_out + kDiag);
     h->partials = (double *)(ws + L.partials);
     h->rho_snap = (double *)(ws + L.rho_snap);
     h->cur = (void *)(ws + L.bufA);
@@ -1424,6 +1445,7 @@ int32_t lbm_get_fusion(const lbm_handle *h) { return h ? h->fuse : -1; }
 lbm_status lbm_autotune(lbm_handle *h, double out[3])
 {
     if (!h) return LBM_ERR_INVALID_ARG;
+    const SpareErrors spare(&h, 1);
     const int align = strip_align(h->p.storage);
     // single steps, always timed; launches cur -> nxt without swapping, so the
     // state is not advanced
@@ -1697,6 +1719,8 @@ lbm_status lbm_batch_autotune(lbm_batch *b, double out[3])
 {
     if (!b) return LBM_ERR_INVALID_ARG;
     if (b->members.empty()) return LBM_OK;
+    // the tables uploaded for timing hold the members' spare error words
+    std::optional<SpareErrors> spare(std::in_place, b->members.data(), b->members.size());
     const bool try_two = b->fuse_max == 2;
     // single steps, always timed (a batch of many small lattices can be
     // faster one step per launch); the counters stay 0 while timing, so every
@@ -1781,6 +1805,8 @@ lbm_status lbm_batch_autotune(lbm_batch *b, double out[3])
     }
     const bool two = try_two && best2 <= best1;
     b->fuse_max = two ? 2 : 1;
+    spare.reset();
+    b->table_valid = false;
     const lbm_status st = batch_upload(b);
     if (st != LBM_OK) return st;
     if (out) {
