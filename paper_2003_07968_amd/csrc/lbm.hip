@@ -6,10 +6,10 @@
 // instantiated in lbm_inst.hip.
 #include "lbm_internal.h"
 #include "lbm_probe.h"
+#include "host_words.h"
 #include "lbm_kernels.hpp"
 
 #include <algorithm>
-#include <atomic>
 #include <cstring>
 #include <mutex>
 #include <optional>
@@ -75,7 +75,8 @@ __global__ __launch_bounds__(256) void reduce_partials_host(const double *__rest
 }
 
 // Error words of up to kHostWords lattices to page-locked host memory.
-constexpr int kHostWords = 32;
+using lbm_host::HostWords;
+using lbm_host::kHostWords;
 struct ErrorWords {
     const unsigned long long *p[kHostWords];
 };
@@ -170,72 +171,6 @@ hipError_t scratch_on_device(int dev, double **out)
     *out = g_scratch_ptr[dev];
     return hipSuccess;
 }
-}  // namespace
-
-// ---- Host words ----
-//
-// Where the calls that wait for the stream read their small results (error
-// words, diagnostics): a kernel writes them to page-locked host memory, the
-// host reads them after its one wait.  A copy to the caller's pageable memory
-// costs a staging copy and a second wait in the runtime (lbm_sync of an idle
-// stream: 20 us with the copy, 11.5 us with the words).
-//
-// One page of kHostSlots slots of kHostWords words for the whole process,
-// allocated at the first use and kept; a call holds a slot from its launch to
-// the end of its wait.  Without a page or a free slot (more than kHostSlots
-// calls at once) the calls use the copies.  A slot whose wait failed is not
-// used again: a kernel may still write to it.
-namespace {
-constexpr int kHostSlots = 16;
-std::once_flag g_host_once;
-unsigned long long *g_host_page;  // null: none
-std::atomic<uint32_t> g_host_busy{0};
-
-struct HostWords {
-    unsigned long long *w = nullptr;  // null: no slot
-    int slot = 0;
-
-    HostWords() = default;
-    HostWords(const HostWords &) = delete;
-    HostWords &operator=(const HostWords &) = delete;
-
-    // Take a slot for work on a stream of device `dev`.
-    explicit HostWords(int dev)
-    {
-        int cur = -1;
-        // a launch needs the stream's device current, which a copy does not
-        if (hipGetDevice(&cur) != hipSuccess || cur != dev) return;
-        std::call_once(g_host_once, [] {
-            // allocating is allowed while another thread captures a graph
-            // in the global mode only with this thread's mode relaxed
-            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-            if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
-            void *p = nullptr;
-            if (hipHostMalloc(&p, kHostSlots * kHostWords * sizeof(*g_host_page),
-                              hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
-                g_host_page = (unsigned long long *)p;
-            else
-                (void)hipGetLastError();
-            (void)hipThreadExchangeStreamCaptureMode(&mode);
-        });
-        if (!g_host_page) return;
-        uint32_t busy = g_host_busy.load(std::memory_order_relaxed);
-        do {
-            const uint32_t open = ~busy & ((1u << kHostSlots) - 1u);
-            if (open == 0) return;
-            slot = __builtin_ctz(open);
-        } while (!g_host_busy.compare_exchange_weak(busy, busy | (1u << slot),
-                                                    std::memory_order_acquire));
-        w = g_host_page + (size_t)slot * kHostWords;
-    }
-
-    // After a successful wait for the work that wrote the slot.
-    void give_back()
-    {
-        if (w) g_host_busy.fetch_and(~(1u << slot), std::memory_order_release);
-        w = nullptr;
-    }
-};
 }  // namespace
 
 struct lbm_batch {
@@ -806,11 +741,15 @@ lbm_status read_sticky_copy(lbm_handle *h)
 
 lbm_status read_sticky(lbm_handle *h)
 {
-    HostWords host(h->device);
+    HostWords host(h->device, h->stream);
     if (!host.w) return read_sticky_copy(h);
     hipLaunchKernelGGL(publish_error, dim3(1), dim3(1), 0, h->stream, h->err, host.w);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) {
+        host.give_back();
+        return dev_fail(h, e, "reading the error word");
+    }
+    e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return dev_fail(h, e, "reading the error word");
     const unsigned long long key = host.w[0];
     host.give_back();
@@ -1292,12 +1231,15 @@ lbm_status lbm_diagnostics(lbm_handle *h, double out[6])
     if (!h || !out) return LBM_ERR_INVALID_ARG;
     hipError_t e = run_sweep<kDiagnostics>(h, h->cur, nullptr, Fields{});
     if (e != hipSuccess) return dev_fail(h, e, "launching the diagnostics kernel");
-    HostWords host(h->device);
+    HostWords host(h->device, h->stream);
     if (host.w) {
         hipLaunchKernelGGL(reduce_partials_host, dim3(1), dim3(256), 0, h->stream, h->partials,
                            h->tiles.ntiles, h->err, (double *)host.w);
         e = hipGetLastError();
-        if (e != hipSuccess) return dev_fail(h, e, "launching the reduction kernel");
+        if (e != hipSuccess) {
+            host.give_back();
+            return dev_fail(h, e, "launching the reduction kernel");
+        }
         e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) return dev_fail(h, e, "reading the diagnostics");
         std::memcpy(out, host.w, kDiag * sizeof(double));
@@ -1928,7 +1870,8 @@ void read_errors(lbm_handle *const *h, int n, lbm_status *st)
 {
     for (int k0 = 0; k0 < n; k0 += kHostWords) {
         const int m = std::min(kHostWords, n - k0);
-        HostWords host(h[k0]->device);
+        const hipStream_t stream = h[k0]->stream;
+        HostWords host(h[k0]->device, stream);
         if (!host.w) {
             for (int k = 0; k < m; ++k)
                 st[k0 + k] = read_sticky_copy(h[k0 + k]);
@@ -1937,14 +1880,14 @@ void read_errors(lbm_handle *const *h, int n, lbm_status *st)
         ErrorWords w{};
         for (int k = 0; k < m; ++k)
             w.p[k] = h[k0 + k]->err;
-        const hipStream_t stream = h[k0]->stream;
         hipLaunchKernelGGL(publish_errors, dim3(1), dim3(64), 0, stream, w, m, host.w);
         hipError_t e = hipGetLastError();
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
+        const bool launched = e == hipSuccess;
+        if (launched) e = hipStreamSynchronize(stream);
         for (int k = 0; k < m; ++k)
             st[k0 + k] = e == hipSuccess ? set_sticky(h[k0 + k], host.w[k])
                                          : dev_fail(h[k0 + k], e, "reading the error words");
-        if (e == hipSuccess) host.give_back();
+        if (e == hipSuccess || !launched) host.give_back();
     }
 }
 
