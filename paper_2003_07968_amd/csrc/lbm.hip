@@ -743,8 +743,11 @@ lbm_status read_sticky(lbm_handle *h)
 {
     HostWords host(h->device, h->stream);
     if (!host.w) return read_sticky_copy(h);
-    hipLaunchKernelGGL(publish_error, dim3(1), dim3(1), 0, h->stream, h->err, host.w);
-    hipError_t e = hipGetLastError();
+    // (the launch's own status: the last error may be one that the caller's
+    // own HIP calls left, which a copy does not report)
+    void *args[] = {&h->err, &host.w};
+    hipError_t e =
+        hipLaunchKernel((const void *)publish_error, dim3(1), dim3(1), args, 0, h->stream);
     if (e != hipSuccess) {
         host.give_back();
         return dev_fail(h, e, "reading the error word");
@@ -1880,8 +1883,9 @@ void read_errors(lbm_handle *const *h, int n, lbm_status *st)
         ErrorWords w{};
         for (int k = 0; k < m; ++k)
             w.p[k] = h[k0 + k]->err;
-        hipLaunchKernelGGL(publish_errors, dim3(1), dim3(64), 0, stream, w, m, host.w);
-        hipError_t e = hipGetLastError();
+        void *args[] = {&w, (void *)&m, &host.w};
+        hipError_t e =
+            hipLaunchKernel((const void *)publish_errors, dim3(1), dim3(64), args, 0, stream);
         const bool launched = e == hipSuccess;
         if (launched) e = hipStreamSynchronize(stream);
         for (int k = 0; k < m; ++k)
