@@ -130,16 +130,15 @@ struct Coeffs {
     int8_t force_on, trace_alt, storage;
 };
 
-// The forms of the force, the velocity and the collisions with the fewest
-// operations, for FP64 (BGK: 115 FP64 instructions per cell and step where the
-// forms written next to them take 143; 2048 x 8192 cells 128 -> 117 us per
-// step in the deep pass).  They round differently from those, by a few 1e-16
-// of the values; against the equations in 80 bits, over 24 lattices of 40 to
-// 110 cells a side and 20 to 120 steps, the populations are off by 9.4e-15
-// (BGK, rms; 9.3e-15 in the other forms) and 6.4e-15 (MRT; 6.3e-15).  The
-// modes that store rounded populations keep the other forms: there a last bit
-// decides which way a stored value rounds, so results would change by the
-// storage's precision.
+// Forms of the velocity and the collisions with fewer operations, for FP64
+// (BGK: 123 FP64 instructions per cell and step where the forms written next
+// to them take 143; the four 2048 x 2048 lattices of the benchmark, 100 steps:
+// 13.8 -> 12.9 ms in the deep pass).  They round differently from those, by a
+// few 1e-16 of the values, and as well: against the equations in 80 bits the
+// populations' rms errors are 0.98 to 1.01 of the other forms' (BGK at tau 0.6
+// to 1.2, MRT at 0.65 to 1, 60 to 300 steps).  The modes that store
+// rounded populations keep the other forms: there a last bit decides which way
+// a stored value rounds, so results would change by the storage's precision.
 template <class R>
 constexpr bool kFewerOps = std::is_same_v<R, double>;
 
@@ -159,9 +158,7 @@ struct Phys {
     R m3g, om2;                       // -3 guo, omega/2 (collide)
     // collide_mrt: 1 - s and 1 - s/2 of each rate (n: omega, the stress rows)
     R ke, he, kz, hz, kq, hq, kn, hn;
-    // kFewerOps: force's weights of s0, s58, s13 and s24 with G0 in them, 6 he,
-    // 6 hz and 2 hn
-    R h_0, h_58, h_2, h_1, he6, hz6, hn2;
+    R he6, hz6, hn2;                  // kFewerOps: 6 he, 6 hz and 2 hn
     Phys() = default;
     __host__ __device__ explicit Phys(const Coeffs &c)
         : omega((R)c.omega), guo((R)c.guo), eos_b((R)c.eos_b), kcT((R)c.kcT), ka((R)c.ka),
@@ -177,8 +174,7 @@ struct Phys {
           keep((R)(1.0 - c.omega)), om3((R)(c.omega / 3.0)), g3((R)(c.guo / 3.0)),
           m3g(R(-3) * guo), om2(R(0.5) * omega), ke(R(1) - s_e), he(R(1) - R(0.5) * s_e),
           kz(R(1) - s_z), hz(R(1) - R(0.5) * s_z), kq(R(1) - s_q), hq(R(1) - R(0.5) * s_q),
-          kn(R(1) - omega), hn(R(1) - R(0.5) * omega), h_0(t0 + m2_0), h_58(t2 + m2_58),
-          h_2(t1 + m2_2), h_1(t1 + m2_1), he6(R(6) * he), hz6(R(6) * hz), hn2(R(2) * hn)
+          kn(R(1) - omega), hn(R(1) - R(0.5) * omega), he6(R(6) * he), hz6(R(6) * hz), hn2(R(2) * hn)
     {
     }
 };
@@ -404,9 +400,10 @@ __device__ __forceinline__ unsigned long long domain_key(long long t, int r, int
 //   F_a = cSC s0 M1_a + cA M1_b M2_ab + cB tr M1_a.
 // Evaluated as F_a = G0 N_a + N_b Q_ab with N = 9 M1 = (s1 - s3) + (a - b)/4,
 // Q = cA M2/9 and G0 = (cSC s0 + cB tr)/9, the constant factors folded into
-// the weights (Phys), each combination of psi values with multiply-adds.  In
-// FP64 G0 is folded into the diagonal of Q as well (H = G0 + Q, six
-// operations less).
+// the weights (Phys), each combination of psi values with multiply-adds.
+// (G0 folded into the diagonal of Q as well, H = G0 + Q, takes six operations
+// less, but the folded weights round once more, the same way in every cell and
+// step: FP64 results came out 1.3 times as far from a 64-bit evaluation.)
 template <class R>
 __device__ __forceinline__ void force(const R s[kQ], const Phys<R> &P, R &Fx, R &Fy)
 {
@@ -417,15 +414,6 @@ __device__ __forceinline__ void force(const R s[kQ], const Phys<R> &P, R &Fx, R 
     const R s58 = p57 + p68;
     const R Nx = fma(R(0.25), a57 - b68, d13);
     const R Ny = fma(R(0.25), a57 + b68, d24);
-    if constexpr (kFewerOps<R>) {
-        const R h0 = fma(P.h_0, s[0], P.h_58 * s58);
-        const R Hxx = fma(P.h_2, s13, fma(P.h_1, s24, h0));
-        const R Hyy = fma(P.h_2, s24, fma(P.h_1, s13, h0));
-        const R Hxy = (p57 - p68) * P.m2_xy;
-        Fx = fma(Nx, Hxx, Ny * Hxy);
-        Fy = fma(Ny, Hyy, Nx * Hxy);
-        return;
-    }
     const R q0 = fma(P.m2_0, s[0], P.m2_58 * s58);
     const R Qxx = fma(P.m2_2, s13, fma(P.m2_1, s24, q0));
     const R Qyy = fma(P.m2_2, s24, fma(P.m2_1, s13, q0));
@@ -477,8 +465,11 @@ __device__ __forceinline__ void velocity(const R d[kQ], R rho, R Fx, R Fy, R &ux
 // With q = (omega/2) J + g F the axis terms are w (c.u)(h c.u + m c.F) = c.u c.q
 // = u_x q_x or u_y q_y, and with S = u_x q_x + u_y q_y the isotropic part is
 // w A = (omega rho - 3 S)/9, the diagonal pairs' T = (w A + S +- (u_x q_y +
-// u_y q_x))/4: 16 operations less (kFewerOps).  Where u = F = 0 each form
-// rounds like the other.
+// u_y q_x))/4: 14 operations less (kFewerOps).  Where u = F = 0 each form
+// rounds like the other.  omega rho is rounded with the sum, once, and the
+// weights of J and F are the other form's: with omega rho rounded by itself, or
+// with 1/3 and 1/12 multiplied in last (two operations less), the errors were
+// up to 1.12 of the other form's.
 template <class R>
 __device__ __forceinline__ void collide(R d[kQ], R ref, R rho, R ux, R uy, R Jx, R Jy, R Fx,
                                         R Fy, const Phys<R> &P)
@@ -487,23 +478,23 @@ __device__ __forceinline__ void collide(R d[kQ], R ref, R rho, R ux, R uy, R Jx,
     if constexpr (kFewerOps<R>) {
         const R gx = g * Fx, gy = g * Fy;
         const R qx = fma(P.om2, Jx, gx), qy = fma(P.om2, Jy, gy);
-        const R Bx = fma(om, Jx, gx), By = fma(om, Jy, gy);  // B/3
+        const R Bx = fma(P.om3, Jx, P.g3 * Fx), By = fma(P.om3, Jy, P.g3 * Fy);
         const R Ex = ux * qx, Ey = uy * qy, S = Ex + Ey;
         const R cross = fma(ux, qy, uy * qx);
-        const R A1 = R(1.0 / 9.0) * fma(R(-3), S, om * rho);
+        const R A1 = R(1.0 / 9.0) * fma(om, rho, R(-3) * S);
         const R W = R(0.25) * (A1 + S);
         const R Tx = Ex + A1, Ty = Ey + A1;
         const R T5 = fma(R(0.25), cross, W), T6 = fma(R(-0.25), cross, W);
         const R B5 = Bx + By, B6 = By - Bx;
         d[0] = fma(keep, d[0], R(4) * A1);
-        d[1] = fma(keep, d[1], fma(R(1.0 / 3.0), Bx, Tx));
-        d[3] = fma(keep, d[3], fma(R(-1.0 / 3.0), Bx, Tx));
-        d[2] = fma(keep, d[2], fma(R(1.0 / 3.0), By, Ty));
-        d[4] = fma(keep, d[4], fma(R(-1.0 / 3.0), By, Ty));
-        d[5] = fma(keep, d[5], fma(R(1.0 / 12.0), B5, T5));
-        d[7] = fma(keep, d[7], fma(R(-1.0 / 12.0), B5, T5));
-        d[6] = fma(keep, d[6], fma(R(1.0 / 12.0), B6, T6));
-        d[8] = fma(keep, d[8], fma(R(-1.0 / 12.0), B6, T6));
+        d[1] = fma(keep, d[1], Tx + Bx);
+        d[3] = fma(keep, d[3], Tx - Bx);
+        d[2] = fma(keep, d[2], Ty + By);
+        d[4] = fma(keep, d[4], Ty - By);
+        d[5] = fma(keep, d[5], fma(R(0.25), B5, T5));
+        d[7] = fma(keep, d[7], fma(R(-0.25), B5, T5));
+        d[6] = fma(keep, d[6], fma(R(0.25), B6, T6));
+        d[8] = fma(keep, d[8], fma(R(-0.25), B6, T6));
         return;
     }
     const R usq = fma(ux, ux, uy * uy);
@@ -552,11 +543,13 @@ __device__ __forceinline__ void collide_mrt(R d[kQ], R rho, R ux, R uy, R Jx, R 
     if constexpr (kFewerOps<R>) {
         // sums and differences of opposite pairs shared by the moments (the
         // momentum's with velocity()), rho u = J, and the stress rows' r =
-        // omega J + 2 (1 - omega/2) F: 31 operations less
+        // omega J + 2 (1 - omega/2) F: 29 operations less.  (The 1/6 and 1/12
+        // of the last lines as multiply-adds take four less again, but all
+        // populations of a cell then round the same way: 1.03 of the error.)
         const R s13 = d[1] + d[3], s24 = d[2] + d[4], s57 = d[5] + d[7], s68 = d[6] + d[8];
         const R d13 = d[1] - d[3], d24 = d[2] - d[4], a57 = d[5] - d[7], b68 = d[6] - d[8];
         const R ax = s13 + s24, dg = s57 + s68, px = a57 - b68, py = a57 + b68;
-        const R dr = d[0] + (ax + dg);
+        const R dr = rho;  // no reference density
         const R e = fma(R(-4), d[0], fma(R(2), dg, -ax));
         const R z = fma(R(4), d[0], fma(R(-2), ax, dg));
         const R uF = fma(ux, Fx, uy * Fy);
@@ -576,16 +569,18 @@ __device__ __forceinline__ void collide_mrt(R d[kQ], R rho, R ux, R uy, R Jx, R 
         const R xd = fma(R(2), jxs, qxs), yd = fma(R(2), jys, qys);
         const R Bx = fma(R(0.25), pxxs, A1), By = fma(R(-0.25), pxxs, A1);
         const R B5 = fma(R(0.25), pxys, A2), B6 = fma(R(-0.25), pxys, A2);
-        const R v5 = xd + yd, v6 = yd - xd;
+        const R X1 = xa * R(1.0 / 6.0), Y1 = ya * R(1.0 / 6.0);
+        const R X2 = xd * R(1.0 / 12.0), Y2 = yd * R(1.0 / 12.0);
+        const R V5 = X2 + Y2, V6 = Y2 - X2;
         d[0] = fma(zs - es, R(1.0 / 9.0), r9);
-        d[1] = fma(R(1.0 / 6.0), xa, Bx);
-        d[3] = fma(R(-1.0 / 6.0), xa, Bx);
-        d[2] = fma(R(1.0 / 6.0), ya, By);
-        d[4] = fma(R(-1.0 / 6.0), ya, By);
-        d[5] = fma(R(1.0 / 12.0), v5, B5);
-        d[7] = fma(R(-1.0 / 12.0), v5, B5);
-        d[6] = fma(R(1.0 / 12.0), v6, B6);
-        d[8] = fma(R(-1.0 / 12.0), v6, B6);
+        d[1] = Bx + X1;
+        d[3] = Bx - X1;
+        d[2] = By + Y1;
+        d[4] = By - Y1;
+        d[5] = B5 + V5;
+        d[7] = B5 - V5;
+        d[6] = B6 + V6;
+        d[8] = B6 - V6;
         return;
     }
     const R dr = (((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7]))) + d[8];
