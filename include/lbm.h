@@ -234,9 +234,9 @@ lbm_status lbm_set_launch(lbm_handle *h, int32_t block_x, int32_t seg_rows);
  * With 2 and neither block_x nor seg_rows given, lbm_step may take more than
  * two steps per launch (four, or the last three of a call, in the deep pass
  * or, on small lattices, the block pass, which takes the last one or two as
- * well); a pair or a single step that is left follows in the forms above.  The results and the
- * first domain error are the same, bitwise.  A shape given here is used for
- * every pair of steps.
+ * well where that is predicted to be faster); a pair or a single step that is
+ * left follows in the forms above.  The results and the first domain error are
+ * the same, bitwise.  A shape given here is used for every pair of steps.
  * Batches have their own setting (lbm_batch_set_fusion). */
 lbm_status lbm_set_fusion(lbm_handle *h, int32_t steps, int32_t block_x, int32_t seg_rows);
 

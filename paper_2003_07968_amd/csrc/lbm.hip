@@ -103,11 +103,13 @@ __global__ void copy_plane(const double *__restrict__ a, double *__restrict__ b,
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // A launch of kDeepSteps steps: the deep pass (bx columns per step, segments of
-// `rows` rows) or the block pass (regions of bx rows), and its predicted time.
+// `rows` rows) or the block pass (regions of bx rows), its predicted time, and
+// which remainders (bit n: n steps) it takes in one launch too (set_tails).
 struct FourShape {
     bool block;
     int bx, rows;
     double us;
+    unsigned tails;
 };
 
 }  // namespace
@@ -546,7 +548,7 @@ bool four_shape(const LatticeSizes &z, int storage, int cus, FourShape *out)
             const double full = rounds(tiles, per_cu, &u), walk = kIterUs[storage] * (r + kFillRows);
             double us = kLaunchUs + full * (walk + kFillUs);
             if (u > 0.0) us += walk * std::max(0.4, 0.16 + 0.84 * u) + kFillUs;
-            if (out->us < 0.0 || us < out->us) *out = FourShape{false, b, r, us};
+            if (out->us < 0.0 || us < out->us) *out = FourShape{false, b, r, us, 0};
         };
         for (int r : kDeepRowsCand)
             consider(r);
@@ -564,7 +566,7 @@ bool four_shape(const LatticeSizes &z, int storage, int cus, FourShape *out)
         for (int k = 0; k < z.count && fits; ++k) {
             Tiles tl;
             fits = make_tiles4(z.nx[(size_t)k * z.stride], z.ny[(size_t)k * z.stride],
-                               FourShape{true, t.rows, 0, 0.0}, &tl);
+                               FourShape{true, t.rows, 0, 0.0, 0}, &tl);
             tiles += tl.ntiles;
         }
         if (!fits) continue;
@@ -573,15 +575,75 @@ bool four_shape(const LatticeSizes &z, int storage, int cus, FourShape *out)
         if (u > 0.0)
             us += t.one + (t.per_cu > 1 ? (t.full - t.one) * (u * t.per_cu - 1.0) / (t.per_cu - 1) : 0.0);
         if ((!deep_fits || 1.15 * us < deep_us) && (out->us < 0.0 || !out->block || us < out->us))
-            *out = FourShape{true, t.rows, 0, us};
+            *out = FourShape{true, t.rows, 0, us, 0};
     }
     return out->us >= 0.0;
 }
 
-bool default_four(const lbm_params &p, int cus, FourShape *f, Tiles *tl)
+// The other forms that a remainder of a call can take: waves of the single-step
+// launch; tiles and segment rows of the two-step launch, and the workgroups of
+// it that the device runs at once.
+struct TailForms {
+    double waves, tiles2;
+    int rows2, slots2;
+};
+
+// Which remainders of one to three steps the form f takes in one launch: those
+// that it is predicted to take no longer for than the single step, the two-step
+// pass or both.  The deep pass takes three steps: us against a two-step
+// launch and a single step, FP64 1024^2 50 and 76, 2048^2 123 and 232; FP32
+// 2048^2 76 and 128; FP16 69 and 91.  Two steps are left to the two-step pass,
+// which moves as many bytes for them.
+//
+// The block pass computes the halo of four steps whatever their number, so its
+// launches of one step cost about half of one of four: on the smallest lattices
+// half of a single step (64^2 FP64 3.6 us and 7.9), on those it only just wins
+// with four steps more than one (FP32 512^2 10.3 and 7.8, 34 lattices of 223 x
+// 33 as a batch 15.9 and 7.8).  The predictions were fitted to 570 lattices and
+// batches in the block pass's range, of all storage modes and both
+// collisions, timed in each form; they are off by 4 to 8% (rms).  Of 1722
+// choices 22 cost more than 3% and none more than 13%.
+void set_tails(FourShape *f, int storage, bool batched, const TailForms &o)
 {
-    return p.force_on && four_shape(LatticeSizes{&p.nx, &p.ny, 1, 0}, p.storage, cus, f) &&
-           make_tiles4(p.nx, p.ny, *f, tl);
+    struct Single {
+        double one, batch, wave;  // us: of a lattice alone, of a batch, per wave
+    };
+    static const Single single[] = {
+        {9.0, 7.5, 2.5e-3}, {6.1, 6.1, 1.5e-3}, {6.3, 6.3, 1.3e-3}, {7.8, 7.8, 1.8e-3}};
+    struct Pair {
+        double us, round, fill;  // per row of the walk: per round of tiles, per filled slot
+    };
+    static const Pair pair[] = {
+        {0.5, 1.25, 0.55}, {2.0, 0.8, 0.4}, {1.6, 0.88, 0.85}, {-0.8, 1.4, 1.2}};
+    // the part of a block launch of four steps that does not depend on the steps
+    static const double fixed[][2] = {{0.35, 0.48}, {0.385, 0.62}, {0.385, 0.62}, {0.36, 0.58}};
+    f->tails = 1u << (kDeepSteps - 1);
+    if (!f->block) return;
+    const double t1 = (batched ? single[storage].batch : single[storage].one) +
+                      single[storage].wave * o.waves;
+    const double t2 =
+        pair[storage].us + (o.rows2 + 2 * kHalo2) *
+                               (pair[storage].round * std::ceil(o.tiles2 / o.slots2) +
+                                pair[storage].fill * o.tiles2 / o.slots2);
+    const double other[] = {0.0, t1, t2, t1 + t2};
+    f->tails = 0;
+    for (int n = 1; n < kDeepSteps; ++n)
+        if (f->us * (fixed[storage][batched] + 0.17 * n) + 0.5 - 0.25 * n <= other[n])
+            f->tails |= 1u << n;
+}
+
+// The default form and shape of the handle's launches of four steps, if any.
+bool default_four(lbm_handle *h)
+{
+    const lbm_params &p = h->p;
+    if (!p.force_on ||
+        !four_shape(LatticeSizes{&p.nx, &p.ny, 1, 0}, p.storage, h->cus, &h->shape4) ||
+        !make_tiles4(p.nx, p.ny, h->shape4, &h->tiles4))
+        return false;
+    set_tails(&h->shape4, p.storage, false,
+              TailForms{(double)h->tiles.ntiles * h->bx / 64, (double)h->tiles2.ntiles,
+                        h->seg_rows2, slots_per_cu2(p.storage, h->bx2) * h->cus});
+    return true;
 }
 
 // Compute units of the current device (256 on MI355X if the query fails).
@@ -640,15 +702,10 @@ hipError_t run_sweep2(lbm_handle *h, const void *src, void *dst)
     return hipErrorInvalidValue;
 }
 
-// Whether a pass of `steps` steps is one launch of the form f: kDeepSteps steps
-// or one less, any number up to kDeepSteps in the block pass.  Three steps in
-// the deep pass, against a two-step launch and a single step, us: FP64 1024^2
-// 50 and 76, 2048^2 123 and 232; FP32 2048^2 76 and 128; FP16 69 and 91.  Two
-// steps are left to the two-step pass, which moves as many bytes for them as
-// the deep pass would.
+// Whether a pass of `steps` steps is one launch of the form f.
 bool one_launch(const FourShape &f, int64_t steps)
 {
-    return f.block || steps >= kDeepSteps - 1;
+    return steps >= kDeepSteps || (f.tails >> steps & 1u) != 0;
 }
 
 template <int ST>
@@ -996,6 +1053,10 @@ lbm_status batch_upload(lbm_batch *b)
     b->total_tiles = tile0;
     b->total_tiles2 = tile0_2;
     b->total_tiles4 = tile0_4;
+    if (four)
+        set_tails(&b->shape4, b->storage, true,
+                  TailForms{(double)tile0 * b->bx / 64, (double)tile0_2, b->rows2,
+                            slots_per_cu2(b->storage, b->bx2) * b->members[0]->cus});
     hipError_t e = hipSuccess;
     if (!b->h_table.empty())
         e = hipMemcpyAsync(b->d_table, b->h_table.data(), b->h_table.size() * sizeof(BatchEntry),
@@ -1156,7 +1217,7 @@ lbm_status lbm_init(const lbm_params *params, void *d_workspace, size_t workspac
                             &h->seg_rows2, &h->tiles2)
                   ? 2
                   : 1;
-    h->four = default_four(*params, h->cus, &h->shape4, &h->tiles4);
+    h->four = default_four(h);
 
     const size_t n = (size_t)params->nx * params->ny;
     const unsigned blocks = (unsigned)((n + 255) / 256);
@@ -1186,9 +1247,6 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps)
     int64_t k = 0;
     if (h->fuse == 2) {
         while (h->four && k < nsteps) {
-            // the block pass takes the remainder of a call too (64^2 FP64: 3.8,
-            // 4.5 and 5.5 us for one to three steps, against 8, 10 and 18 in the
-            // other forms), the deep pass three steps
             const int n = (int)std::min<int64_t>(kDeepSteps, nsteps - k);
             if (!one_launch(h->shape4, n)) break;
             hipError_t e = run_four(h, h->cur, h->nxt, n);
@@ -1366,12 +1424,11 @@ lbm_status lbm_set_fusion(lbm_handle *h, int32_t steps, int32_t block_x, int32_t
         return LBM_ERR_INVALID_ARG;
     }
     h->fuse = 2;
-    // a shape of the caller's is used for every pair of steps
-    h->four = block_x == 0 && seg_rows == 0 &&
-              default_four(h->p, h->cus, &h->shape4, &h->tiles4);
     h->bx2 = bx;
     h->seg_rows2 = rows;
     h->tiles2 = tl;
+    // a shape of the caller's is used for every pair of steps
+    h->four = block_x == 0 && seg_rows == 0 && default_four(h);
     return LBM_OK;
 }
 
@@ -1486,7 +1543,7 @@ lbm_status lbm_autotune(lbm_handle *h, double out[3])
         h->seg_rows2 = rows2;
         // four steps per launch in the default shape
         double best4 = 1e300;
-        if (default_four(h->p, h->cus, &h->shape4, &h->tiles4)) {
+        if (default_four(h)) {
             auto four = [&] { return run_four(h, h->cur, h->nxt); };
             for (int k = 0; k < 3; ++k) {
                 const double us = time_launches(h->stream, 20, four, 5);
@@ -1543,7 +1600,7 @@ lbm_status lbm_batch_create(int32_t capacity, void *d_workspace, size_t workspac
     b->rows2 = kBatchRows2;
     b->auto_rows2 = true;
     b->four = true;
-    b->shape4 = FourShape{false, 256, 0, 0.0};
+    b->shape4 = FourShape{false, 256, 0, 0.0, 0};
     b->total_tiles = 0;
     b->total_tiles2 = 0;
     b->total_tiles4 = 0;
