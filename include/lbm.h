@@ -243,6 +243,27 @@ lbm_status lbm_set_fusion(lbm_handle *h, int32_t steps, int32_t block_x, int32_t
 /* Time steps per pass in use (1 or 2); -1 for a NULL handle. */
 int32_t lbm_get_fusion(const lbm_handle *h);
 
+/* Passes of more than two steps (see lbm_set_fusion).  form:
+ *   LBM_PASS_DEFAULT  the library's choice, as after lbm_init (width and
+ *                     seg_rows 0; also lbm_set_fusion(h, 2, 0, 0));
+ *   LBM_PASS_SHORT    none: one or two steps per launch (width, seg_rows 0);
+ *   LBM_PASS_DEEP     the deep pass: width 64, 128 or 256 columns of a
+ *                     workgroup, segments of seg_rows >= 1 rows;
+ *   LBM_PASS_BLOCK    the block pass: regions of width 16, 20, 24 or 32 rows,
+ *                     seg_rows 0, for every remainder of a call too.
+ * For callers that have measured a form (lbm_autotune, then lbm_get_pass) and
+ * want it again without the timing, and for tests and profiles of one form.
+ * Results are bitwise the same.  LBM_ERR_INVALID_ARG, nothing changed: other
+ * values, a lattice without the force, or one step per pass (lbm_get_fusion 1)
+ * with the last two forms. */
+enum { LBM_PASS_DEFAULT = -1, LBM_PASS_SHORT = 0, LBM_PASS_DEEP = 1, LBM_PASS_BLOCK = 2 };
+lbm_status lbm_set_pass(lbm_handle *h, int32_t form, int32_t width, int32_t seg_rows);
+
+/* The pass in use while enough steps of a call are left: out[0] = steps per
+ * launch (4, 2 or 1), out[1] = LBM_PASS_SHORT, _DEEP or _BLOCK, out[2] and
+ * out[3] = its width and seg_rows as in lbm_set_pass. */
+lbm_status lbm_get_pass(const lbm_handle *h, int32_t out[4]);
+
 /* The launch shape of the step kernel in use (the two-step pass's when
  * lbm_get_fusion is 2, also where longer passes are taken before it): out[0] =
  * block_x, out[1] = seg_rows, out[2] = workgroups per launch. */
@@ -255,7 +276,8 @@ lbm_status lbm_get_launch(const lbm_handle *h, int32_t out[3]);
  * the fastest per time step, switching to single steps if they win (results
  * are bitwise the same; lbm_get_fusion tells which).  Passes of more than two
  * steps are timed at the library's shape and used while they are the fastest;
- * the shape reported is then the two-step pass's, for the steps they leave.
+ * out then has their time, and the two-step pass's shape, for the steps they
+ * leave (lbm_get_pass has theirs).
  * The timed launches write only the spare population buffer and are not
  * counted as steps, so the state and t are unchanged; a domain error that they
  * meet at t or later is not recorded.  Synchronous; out (may be NULL) receives the
@@ -308,8 +330,9 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps);
  * timed over a few launches, the fastest three again over longer samples;
  * the faster form per time step is kept (lbm_batch_get_fusion tells which).
  * Shapes within about 1% of each other may swap places between calls.
- * Synchronous; out (may be NULL): block_x, seg_rows, microseconds per time
- * step. */
+ * Passes of more than two steps are timed at the library's shape, as in
+ * lbm_autotune (lbm_batch_get_pass tells which won).  Synchronous; out (may be
+ * NULL): block_x, seg_rows, microseconds per time step. */
 lbm_status lbm_batch_autotune(lbm_batch *b, double out[3]);
 
 /* Time steps per batched launch: 2 (the default) or 1.  Results are bitwise
@@ -322,6 +345,15 @@ lbm_status lbm_batch_set_fusion(lbm_batch *b, int32_t steps);
 /* Steps per batched launch in use (1 or 2; -1 for NULL). */
 int32_t lbm_batch_get_fusion(const lbm_batch *b);
 
+/* Passes of more than two steps for the batch, as lbm_set_pass and
+ * lbm_get_pass.  The library's choice is made over all members whenever the
+ * table is written; lbm_batch_get_pass writes it if it is out of date
+ * (synchronous).  LBM_PASS_DEFAULT also takes back what lbm_batch_set_launch
+ * and lbm_batch_autotune have set.  A shape that does not fit a member is
+ * reported by the next lbm_batch_step. */
+lbm_status lbm_batch_set_pass(lbm_batch *b, int32_t form, int32_t width, int32_t seg_rows);
+lbm_status lbm_batch_get_pass(lbm_batch *b, int32_t out[4]);
+
 /* Fix the batch's launch: `steps` per launch (1 or 2) with workgroups of
  * block_x threads walking segments of seg_rows rows.  Two-step pass: block_x
  * 128, 256 or 512, seg_rows >= 1, or 0 for the length chosen at each table
@@ -329,8 +361,8 @@ int32_t lbm_batch_get_fusion(const lbm_batch *b);
  * that form, and longer passes are not used.  Single steps: block_x a multiple
  * of 64 in 64..512, seg_rows >= 1.  Other values: LBM_ERR_INVALID_ARG, nothing
  * changed.  For callers that have measured a shape (lbm_batch_autotune) and
- * want it again without the timing, and for profiling runs that must launch
- * one known shape.  Results are bitwise the same for every shape.  The next
+ * want it again without the timing (where a longer pass won, lbm_batch_set_pass
+ * brings it back), and for profiling runs that must launch one known shape.  Results are bitwise the same for every shape.  The next
  * lbm_batch_step rewrites the table; a shape that needs more workgroups than
  * a launch may have is reported there. */
 lbm_status lbm_batch_set_launch(lbm_batch *b, int32_t steps, int32_t block_x, int32_t seg_rows);

@@ -194,7 +194,8 @@ struct lbm_batch {
     int bx2, rows2;           // two-step shape
     bool auto_rows2;          // rows2 chosen at each upload (until autotuned)
     bool four;                // launches of kDeepSteps steps may be used (no shape was asked for)
-    FourShape shape4;         // their form and shape, chosen at each upload
+    bool four_set;            // shape4 was set by the caller (else chosen at each upload)
+    FourShape shape4;         // their form and shape
     int total_tiles, total_tiles2, total_tiles4;  // total_tiles4 0: not used
     hipGraphExec_t graph;     // kGraphSteps batched steps, valid with the table
     bool graph_valid;
@@ -632,18 +633,40 @@ void set_tails(FourShape *f, int storage, bool batched, const TailForms &o)
             f->tails |= 1u << n;
 }
 
+// Take f for the handle's launches of four steps; false (nothing changed): it
+// does not fit.
+bool use_four(lbm_handle *h, FourShape f)
+{
+    const lbm_params &p = h->p;
+    Tiles tl;
+    if (!p.force_on || !make_tiles4(p.nx, p.ny, f, &tl)) return false;
+    set_tails(&f, p.storage, false,
+              TailForms{(double)h->tiles.ntiles * h->bx / 64, (double)h->tiles2.ntiles,
+                        h->seg_rows2, slots_per_cu2(p.storage, h->bx2) * h->cus});
+    h->shape4 = f;
+    h->tiles4 = tl;
+    return true;
+}
+
 // The default form and shape of the handle's launches of four steps, if any.
 bool default_four(lbm_handle *h)
 {
-    const lbm_params &p = h->p;
-    if (!p.force_on ||
-        !four_shape(LatticeSizes{&p.nx, &p.ny, 1, 0}, p.storage, h->cus, &h->shape4) ||
-        !make_tiles4(p.nx, p.ny, h->shape4, &h->tiles4))
-        return false;
-    set_tails(&h->shape4, p.storage, false,
-              TailForms{(double)h->tiles.ntiles * h->bx / 64, (double)h->tiles2.ntiles,
-                        h->seg_rows2, slots_per_cu2(p.storage, h->bx2) * h->cus});
-    return true;
+    FourShape f;
+    return four_shape(LatticeSizes{&h->p.nx, &h->p.ny, 1, 0}, h->p.storage, h->cus, &f) &&
+           use_four(h, f);
+}
+
+// A form and shape that a caller asks for (lbm_set_pass).  No time is predicted:
+// the block pass takes every remainder.
+bool four_from_args(int32_t form, int32_t width, int32_t seg_rows, FourShape *f)
+{
+    *f = FourShape{form == LBM_PASS_BLOCK, width, seg_rows, 0.0, 0};
+    if (form == LBM_PASS_DEEP)
+        return (width == 64 || width == 128 || width == 256) && seg_rows >= 1;
+    bool rows = false;
+    for (const BlockTime &t : kBlockTimes[0])
+        rows = rows || t.rows == width;
+    return form == LBM_PASS_BLOCK && rows && seg_rows == 0;
 }
 
 // Compute units of the current device (256 on MI355X if the query fails).
@@ -1008,7 +1031,7 @@ lbm_status batch_upload(lbm_batch *b)
         }
     }
     bool four = two && b->four && b->force_on && !b->members.empty();
-    if (four) {
+    if (four && !b->four_set) {
         std::vector<int32_t> sizes;
         for (const lbm_handle *h : b->members) {
             sizes.push_back(h->p.nx);
@@ -1444,6 +1467,44 @@ lbm_status lbm_get_launch(const lbm_handle *h, int32_t out[3])
 
 int32_t lbm_get_fusion(const lbm_handle *h) { return h ? h->fuse : -1; }
 
+lbm_status lbm_set_pass(lbm_handle *h, int32_t form, int32_t width, int32_t seg_rows)
+{
+    if (!h) return LBM_ERR_INVALID_ARG;
+    if (form == LBM_PASS_DEFAULT || form == LBM_PASS_SHORT) {
+        if (width != 0 || seg_rows != 0) {
+            h->last_error = "this form has no width or seg_rows";
+            return LBM_ERR_INVALID_ARG;
+        }
+        if (form == LBM_PASS_DEFAULT) return lbm_set_fusion(h, 2, 0, 0);
+        h->four = false;
+        return LBM_OK;
+    }
+    FourShape f;
+    if (!four_from_args(form, width, seg_rows, &f)) {
+        h->last_error = "deep pass: width 64, 128 or 256 and seg_rows >= 1; block pass: width "
+                        "16, 20, 24 or 32 and seg_rows 0";
+        return LBM_ERR_INVALID_ARG;
+    }
+    if (h->fuse != 2 || !use_four(h, f)) {
+        h->last_error = "needs the force, two steps per pass (lbm_set_fusion) and a shape with "
+                        "fewer workgroups";
+        return LBM_ERR_INVALID_ARG;
+    }
+    h->four = true;
+    return LBM_OK;
+}
+
+lbm_status lbm_get_pass(const lbm_handle *h, int32_t out[4])
+{
+    if (!h || !out) return LBM_ERR_INVALID_ARG;
+    const bool four = h->fuse == 2 && h->four;
+    out[0] = four ? kDeepSteps : h->fuse;
+    out[1] = !four ? LBM_PASS_SHORT : h->shape4.block ? LBM_PASS_BLOCK : LBM_PASS_DEEP;
+    out[2] = four ? h->shape4.bx : 0;
+    out[3] = four && !h->shape4.block ? h->shape4.rows : 0;
+    return LBM_OK;
+}
+
 lbm_status lbm_autotune(lbm_handle *h, double out[3])
 {
     if (!h) return LBM_ERR_INVALID_ARG;
@@ -1600,6 +1661,7 @@ lbm_status lbm_batch_create(int32_t capacity, void *d_workspace, size_t workspac
     b->rows2 = kBatchRows2;
     b->auto_rows2 = true;
     b->four = true;
+    b->four_set = false;
     b->shape4 = FourShape{false, 256, 0, 0.0, 0};
     b->total_tiles = 0;
     b->total_tiles2 = 0;
@@ -1794,6 +1856,7 @@ lbm_status lbm_batch_autotune(lbm_batch *b, double out[3])
         b->rows2 = rows2;
         // four steps per launch in the default shape
         b->four = true;
+        b->four_set = false;
         double best4 = 1e300;
         if (batch_upload(b) == LBM_OK && b->total_tiles4 > 0) {
             auto four = [&] { return batch_launch_steps(b, kDeepSteps, nullptr, 0, 0); };
@@ -1844,7 +1907,7 @@ lbm_status lbm_batch_set_launch(lbm_batch *b, int32_t steps, int32_t block_x, in
             return LBM_ERR_INVALID_ARG;
         }
         b->bx2 = block_x;
-        b->four = false;
+        b->four = b->four_set = false;
         b->auto_rows2 = seg_rows == 0;
         if (seg_rows > 0) b->rows2 = seg_rows;
     } else if (steps == 1) {
@@ -1864,6 +1927,54 @@ lbm_status lbm_batch_set_launch(lbm_batch *b, int32_t steps, int32_t block_x, in
         (void)hipGraphExecDestroy(b->graph);
         b->graph_valid = false;
     }
+    return LBM_OK;
+}
+
+lbm_status lbm_batch_set_pass(lbm_batch *b, int32_t form, int32_t width, int32_t seg_rows)
+{
+    if (!b) return LBM_ERR_INVALID_ARG;
+    if (form == LBM_PASS_DEFAULT || form == LBM_PASS_SHORT) {
+        if (width != 0 || seg_rows != 0) {
+            b->last_error = "this form has no width or seg_rows";
+            return LBM_ERR_INVALID_ARG;
+        }
+        b->four = form == LBM_PASS_DEFAULT;
+        b->four_set = false;
+        if (b->four) {
+            b->fuse_max = 2;
+            b->bx2 = kFuseBx;
+            b->auto_rows2 = true;
+        }
+    } else {
+        FourShape f;
+        if (!four_from_args(form, width, seg_rows, &f) || b->fuse_max != 2) {
+            b->last_error = "deep pass: width 64, 128 or 256 and seg_rows >= 1; block pass: "
+                            "width 16, 20, 24 or 32 and seg_rows 0; two steps per launch";
+            return LBM_ERR_INVALID_ARG;
+        }
+        b->four = b->four_set = true;
+        b->shape4 = f;
+    }
+    b->table_valid = false;
+    if (b->graph_valid) {
+        (void)hipGraphExecDestroy(b->graph);
+        b->graph_valid = false;
+    }
+    return LBM_OK;
+}
+
+lbm_status lbm_batch_get_pass(lbm_batch *b, int32_t out[4])
+{
+    if (!b || !out) return LBM_ERR_INVALID_ARG;
+    if (!b->members.empty() && batch_stale(b)) {
+        const lbm_status st = batch_upload(b);
+        if (st != LBM_OK) return st;
+    }
+    const bool four = !b->members.empty() && b->total_tiles4 > 0;
+    out[0] = four ? kDeepSteps : batch_fuse(b);
+    out[1] = !four ? LBM_PASS_SHORT : b->shape4.block ? LBM_PASS_BLOCK : LBM_PASS_DEEP;
+    out[2] = four ? b->shape4.bx : 0;
+    out[3] = four && !b->shape4.block ? b->shape4.rows : 0;
     return LBM_OK;
 }
 

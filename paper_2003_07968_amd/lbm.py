@@ -28,6 +28,10 @@ LBM_STORE_F64 = 0
 LBM_STORE_F32_SHIFTED = 1
 LBM_STORE_F16_SHIFTED = 2
 LBM_STORE_F16_LOCAL = 3
+LBM_PASS_DEFAULT = -1
+LBM_PASS_SHORT = 0
+LBM_PASS_DEEP = 1
+LBM_PASS_BLOCK = 2
 LBM_COLL_BGK = 0
 LBM_COLL_MRT = 1
 
@@ -109,6 +113,10 @@ def _load():
         lib.lbm_set_fusion.restype = ctypes.c_int
         lib.lbm_get_fusion.argtypes = [H]
         lib.lbm_get_fusion.restype = ctypes.c_int32
+        lib.lbm_set_pass.argtypes = [H, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
+        lib.lbm_set_pass.restype = ctypes.c_int
+        lib.lbm_get_pass.argtypes = [H, ctypes.POINTER(ctypes.c_int32)]
+        lib.lbm_get_pass.restype = ctypes.c_int
         lib.lbm_get_launch.argtypes = [H, ctypes.POINTER(ctypes.c_int32)]
         lib.lbm_get_launch.restype = ctypes.c_int
         lib.lbm_status_string.argtypes = [ctypes.c_int]
@@ -144,6 +152,10 @@ def _load():
         lib.lbm_batch_set_launch.restype = ctypes.c_int
         lib.lbm_batch_get_launch.argtypes = [B, ctypes.POINTER(ctypes.c_int32)]
         lib.lbm_batch_get_launch.restype = ctypes.c_int
+        lib.lbm_batch_set_pass.argtypes = [B, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
+        lib.lbm_batch_set_pass.restype = ctypes.c_int
+        lib.lbm_batch_get_pass.argtypes = [B, ctypes.POINTER(ctypes.c_int32)]
+        lib.lbm_batch_get_pass.restype = ctypes.c_int
         lib.lbm_batch_destroy.argtypes = [B]
         lib.lbm_batch_destroy.restype = None
         lib.lbm_probe_stream_bytes.argtypes = [ctypes.c_int32, ctypes.c_int32]
@@ -184,7 +196,8 @@ EXPORTED = ("lbm_workspace_bytes", "lbm_init", "lbm_step", "lbm_sync", "lbm_mome
             "lbm_last_error", "lbm_destroy", "lbm_server_create", "lbm_server_job_bytes",
             "lbm_server_submit", "lbm_server_advance", "lbm_server_poll",
             "lbm_server_get_stats", "lbm_server_destroy", "lbm_probe_stream_bytes",
-            "lbm_probe_stream")
+            "lbm_probe_stream", "lbm_set_pass", "lbm_get_pass", "lbm_batch_set_pass",
+            "lbm_batch_get_pass")
 
 
 def make_params(p: dict) -> lbm_params:
@@ -281,6 +294,16 @@ def lbm_get_fusion(h):
     return _load().lbm_get_fusion(h)
 
 
+def lbm_set_pass(h, form, width=0, seg_rows=0):
+    _check(h, _load().lbm_set_pass(h, int(form), int(width), int(seg_rows)))
+
+
+def lbm_get_pass(h):
+    out = (ctypes.c_int32 * 4)()
+    _check(h, _load().lbm_get_pass(h, out))
+    return tuple(out)
+
+
 def lbm_get_launch(h):
     out = (ctypes.c_int32 * 3)()
     _check(h, _load().lbm_get_launch(h, out))
@@ -351,6 +374,16 @@ def lbm_batch_get_launch(b):
     out = (ctypes.c_int32 * 3)()
     _check_b(_load().lbm_batch_get_launch(b, out))
     return int(out[0]), int(out[1]), int(out[2])
+
+
+def lbm_batch_set_pass(b, form, width=0, seg_rows=0):
+    _check_b(_load().lbm_batch_set_pass(b, int(form), int(width), int(seg_rows)))
+
+
+def lbm_batch_get_pass(b):
+    out = (ctypes.c_int32 * 4)()
+    _check_b(_load().lbm_batch_get_pass(b, out))
+    return tuple(out)
 
 
 def lbm_probe_stream_bytes(nx, ny):
@@ -517,6 +550,13 @@ class Lattice:
     def launch(self):
         return lbm_get_launch(self.handle)
 
+    def set_pass(self, form, width=0, seg_rows=0):
+        lbm_set_pass(self.handle, form, width, seg_rows)
+
+    def get_pass(self):
+        """(steps per launch, LBM_PASS_ form, width, seg_rows) in use."""
+        return lbm_get_pass(self.handle)
+
     def autotune(self):
         return lbm_autotune(self.handle)
 
@@ -534,7 +574,7 @@ class Lattice:
 
 class Batch:
     """A group of Lattice objects advanced together: one kernel launch covers every
-    member, per two time steps (the two-step pass) or per step."""
+    member, per four time steps, two (the two-step pass) or one."""
 
     def __init__(self, capacity, device="cuda", stream=None):
         self.workspace = torch.empty(lbm_batch_workspace_bytes(capacity), dtype=torch.uint8,
@@ -574,6 +614,13 @@ class Batch:
     def launch(self):
         """(steps per launch, block_x, seg_rows) in use."""
         return lbm_batch_get_launch(self.handle)
+
+    def set_pass(self, form, width=0, seg_rows=0):
+        lbm_batch_set_pass(self.handle, form, width, seg_rows)
+
+    def get_pass(self):
+        """(steps per launch, LBM_PASS_ form, width, seg_rows) in use."""
+        return lbm_batch_get_pass(self.handle)
 
     def close(self):
         if self.handle:
