@@ -12,7 +12,8 @@ once), in the shape that it chooses; what is left of the step count goes
 through the two-step pass and the single step.  --fusion 2 and 1 measure those
 two alone, in a fixed launch shape per storage mode (SLAB_LAUNCH, the fastest
 of launch sweeps of this workload); --launch sets another two-step shape,
---autotune lets the library's batch autotuner pick form and shape.
+--autotune lets the library's batch autotuner pick form and shape (with
+--fusion, the shape of that form).
 --one-by-one gives each lattice launches of its own instead; the default line
 carries that rate too (`one_lattice_per_launch`).  Inputs are resident in HBM
 before timing.
@@ -85,7 +86,7 @@ VALU_PEAK_GIPS = 614.4
 # storage modes whose two-step pass is bound by VALU issue (committed counters)
 ISSUE_BOUND = ("f16", "f16l")
 # time steps that one launch of each kernel takes
-STEPS_PER_LAUNCH = {"deep": 4, "pass2": 2, "step": 1}
+STEPS_PER_LAUNCH = {"deep": 4, "block": 4, "pass2": 2, "step": 1}
 METRIC = "MLUPS/GPU and % HBM roofline (FP64 vs FP32/FP16-shifted); p50/p99 time-to-result"
 N = 2048
 TEMPS = (0.6, 0.7, 0.8, 0.9)
@@ -323,10 +324,15 @@ def run_batch(args):
             batch.set_fusion(args.fusion)
         for lat in lats:
             batch.add(lat)
-        bx, rows, us = batch.autotune()  # shape, and one or two steps per launch
-        fusion = batch.fusion()
-        err(f"batch of {len(lats)} lattices, {cells} cells; autotuned block {bx}, "
-            f"rows {rows}: {us:.1f} us/step")
+        bx, rows, us = batch.autotune()  # form and shape, the fastest per step
+        if args.fusion == 2 and batch.launch()[0] == 2:
+            batch.set_launch(*batch.launch())   # the tuned two-step shape alone
+        used = batch.get_pass()
+        kernel = kernel_of(used)
+        per = STEPS_PER_LAUNCH[kernel]
+        err(f"batch of {len(lats)} lattices, {cells} cells; autotuned: {kernel} pass, {per} "
+            f"step(s) per launch, {f'shape {used[2:]}' if per == 4 else f'block {bx}, rows {rows}'}"
+            f": {us:.1f} us/step")
         batch.step(args.warmup)
         torch.cuda.synchronize()
         e0 = torch.cuda.Event(enable_timing=True)
@@ -380,15 +386,15 @@ def run_batch(args):
                         "T_r U[0.55,0.95], sigma U[1/8,4], R0 U[0.15,0.35] side, seed 6; "
                         "batched launches, autotuned form and shape",
             "storage": storage, "lattices": len(lats), "cells": cells,
-            "steps_per_launch": 1 if fusion == 1 else "4 or 2 (autotuned)",
+            "steps_per_launch": per,
+            "launch_block_x_seg_rows": list(used[2:]) if per == 4 else [bx, rows],
             "bytes_per_cell_update": bpc,
         },
         "roofline": {
             "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
-            "kernel": ("batch_step_kernel (one step per launch)" if fusion == 1 else
-                       "batch_deep_kernel or batch_block_kernel (four steps per launch), "
-                       "or batch2_kernel (two)"),
+            "kernel": f"{KERNEL_NAMES[kernel][1]} "
+                      f"({('one step', 'two steps', None, 'four steps')[per - 1]} per launch)",
             "kernel_avg_ms": None,
         },
         "plain_fp64_sequential": {
@@ -544,6 +550,22 @@ def serving_summary(count):
     return res
 
 
+def kernel_of(get_pass):
+    """The dominant kernel (a key of STEPS_PER_LAUNCH) of a lattice or a batch by its
+    get_pass(): what the library launches, whatever was asked for."""
+    from paper_2003_07968_amd import lbm
+    steps, form = get_pass[:2]
+    if form == lbm.LBM_PASS_SHORT:
+        return "pass2" if steps == 2 else "step"
+    return "block" if form == lbm.LBM_PASS_BLOCK else "deep"
+
+
+KERNEL_NAMES = {"deep": ("deep_kernel", "batch_deep_kernel"),
+                "block": ("block_kernel", "batch_block_kernel"),
+                "pass2": ("sweep2_kernel", "batch2_kernel"),
+                "step": ("sweep_kernel", "batch_step_kernel")}
+
+
 def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=None,
              autotune=False):
     """The four-temperature 2048^2 slab workload in one storage mode.  The four
@@ -562,7 +584,6 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
     from paper_2003_07968_amd import workloads as W
 
     stream = torch.cuda.Stream()  # graphs of the batch cannot be captured on the null stream
-    deep = fusion is None and shape is None   # the library's own choice
     with torch.cuda.stream(stream):
         lats = []
         for tr in TEMPS:
@@ -577,8 +598,6 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
                 lats[-1].set_fusion(fusion)
         if one_by_one:
             batch = None
-            launch = list(lats[0].launch())
-            fus = lats[0].fusion()
         else:
             batch = lbm.Batch(len(lats))
             if fusion is not None:
@@ -587,18 +606,21 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
                 batch.add(lat)
             if autotune:
                 batch.autotune()
-            elif not deep:
+                if fusion == 2 and batch.launch()[0] == 2:
+                    batch.set_launch(*batch.launch())   # the tuned two-step shape alone
+            elif fusion is not None or shape is not None:
                 batch.set_launch(fusion or 2, *(shape or SLAB_LAUNCH[fusion or 2][storage]))
-            fus, bx, rows = batch.launch()
-            launch = [bx, rows]
+        target = lats[0] if one_by_one else batch
+        used = target.get_pass()
         torch.cuda.synchronize()
-        kernel = "deep" if deep else ("pass2" if fus == 2 else "step")
+        kernel = kernel_of(used)
         per = STEPS_PER_LAUNCH[kernel]
-        if deep:
-            launch = None
+        # (block_x, seg_rows); of the block pass, its rows
+        launch = (list(used[2:]) if per == 4 else
+                  list(target.launch())[:2] if one_by_one else list(target.launch())[1:])
         err(f"{storage}: lattices ready, {per} step(s) per launch, "
             f"{'one lattice per launch' if one_by_one else 'four lattices per launch'}, "
-            f"launch shape {launch or 'chosen by the library'}")
+            f"{kernel} pass, launch shape {launch}")
 
         def advance(nsteps):
             if batch is not None:
@@ -649,8 +671,7 @@ def run_slab(storage, collision, fusion, steps, warmup, one_by_one=False, shape=
     launches = len(lats) // per_launch
     launch_ms = (group_ms / (groups * launches) if groups > 0 else
                  gpu_ms / (steps * launches))
-    name = {"deep": ("deep_kernel", "batch_deep_kernel"), "pass2": ("sweep2_kernel", "batch2_kernel"),
-            "step": ("sweep_kernel", "batch_step_kernel")}[kernel][0 if one_by_one else 1]
+    name = KERNEL_NAMES[kernel][0 if one_by_one else 1]
     kname = (f"{name} ({('one step', 'two steps', None, 'four steps')[per - 1]} per launch" +
              ("" if one_by_one else ", four lattices per launch"))
     # what is left, one to three steps, is one launch too
@@ -791,9 +812,10 @@ def main():
             "lattices_per_launch": res["lattices_per_launch"],
             "bytes_per_cell_update": bpu,
             "launch_block_x_seg_rows": list(shape_used) if shape_used else None,
-            "launch_from": ("batch autotuner" if args.autotune else
-                            "library default" if kernel == "deep" or args.one_by_one else
-                            "--launch" if shape else "bench table (SLAB_LAUNCH)"),
+            "launch_from": ("library default" if args.one_by_one else
+                            "batch autotuner" if args.autotune else
+                            "--launch" if shape else
+                            "bench table (SLAB_LAUNCH)" if args.fusion else "library default"),
             "timed_launches": res["timed_launches"],
             "untimed_warmup_steps": res["warmup_steps"],
         },
@@ -824,7 +846,7 @@ def main():
     # the issue-bound two-step modes (FP16 storage, FP32 arithmetic) are priced
     # against the VALU issue rate, the HBM figures kept beside it
     rf = out["roofline"]
-    if kernel != "deep" and args.storage in ISSUE_BOUND and rf["valu"] is not None:
+    if upl < 4 and args.storage in ISSUE_BOUND and rf["valu"] is not None:
         v = rf.pop("valu")
         rf["hbm"] = {k: rf[k] for k in ("achieved", "peak", "unit", "frac")}
         rf.update(bound="alu", achieved=v["achieved"], peak=v["peak"], unit=v["unit"],
