@@ -864,8 +864,8 @@ BatchArgs batch_args(const lbm_batch *b, int steps, const long long *ctr, long l
 }
 
 // One batched launch of `steps` (1, 2 or see batch_long) steps starting where batch_pos says:
-// eager launches pass the position (ctr = nullptr), captured ones their offset
-// from the device counters.
+// eager launches pass the position (ctr = nullptr), captured ones (one or two
+// steps) their offset from the device counters.
 hipError_t batch_launch_steps(lbm_batch *b, int steps, const long long *ctr, long long steps_add,
                               int launches_add)
 {
@@ -1120,8 +1120,8 @@ bool batch_stale(const lbm_batch *b)
     return false;
 }
 
-// Capture kGraphSteps batched steps in a graph: launches of batch_steps(b)
-// steps at their offsets from the device counters, then one kernel that
+// Capture kGraphSteps batched steps in a graph: launches of batch_fuse(b)
+// steps (never the longer passes) at their offsets from the device counters, then one kernel that
 // moves the counters on by the whole graph.  An even number of launches, so
 // a replay leaves every lattice's state in the buffer it started from.
 hipError_t batch_capture(lbm_batch *b)
@@ -1130,7 +1130,7 @@ hipError_t batch_capture(lbm_batch *b)
     hipError_t e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
     hipError_t le = hipSuccess;
-    const int per = batch_steps(b), n = kGraphSteps / per;
+    const int per = batch_fuse(b), n = kGraphSteps / per;
     for (int k = 0; k < n && le == hipSuccess; ++k)
         le = batch_launch_steps(b, per, b->d_ctr, (long long)k * per, k);
     if (le == hipSuccess) {

@@ -198,15 +198,14 @@ __global__ __launch_bounds__(kBlockW *RH, (kBlockWaves<ST, RH>)) void block_kern
                                 xcd_tile(blockIdx.x, tl.ntiles), t, steps, err);
 }
 
-// The block pass over every lattice of a batch.
+// The block pass over every lattice of a batch, `done` steps after the table was
+// written, from the buffers of this parity.
 template <int RH, int T, int ST, int COLL>
 __global__ __launch_bounds__(kBlockW *RH, (kBlockWaves<ST, RH>)) void batch_block_kernel(
-    const BatchEntry *__restrict__ table, int nlat, const long long *__restrict__ d_ctr,
-    long long steps_add, int launches_add, int steps)
+    const BatchEntry *__restrict__ table, int nlat, long long done, int parity, int steps)
 {
-    const BatchPos pos = batch_pos(d_ctr, steps_add, launches_add);
     const BatchTile k = batch_tile<&BatchEntry::tile0_4, &BatchEntry::tl4>(
-        table, nlat, xcd_tile(blockIdx.x, gridDim.x), pos.steps, pos.parity);
+        table, nlat, xcd_tile(blockIdx.x, gridDim.x), done, parity);
     const auto P = in_scalar_registers(Phys<typename Store<ST>::R>(k.c));
     block_tile<RH, T, ST, COLL>(k.src, k.dst, k.c, P, k.tl.nstrips, k.tl.nseg, k.tile, k.t,
                                 steps, k.err);
@@ -247,8 +246,8 @@ hipError_t batch_block_launch_rows(const BatchArgs &a, int steps)
 #define LBM_CASE(RH)                                                                          \
     case RH:                                                                                  \
         hipLaunchKernelGGL((batch_block_kernel<RH, kDeepSteps, ST, COLL>), dim3(a.grid),       \
-                           dim3(kBlockW *RH), 0, a.stream, a.table, a.nlat, a.ctr,            \
-                           a.steps_add, a.launches_add, steps);                               \
+                           dim3(kBlockW *RH), 0, a.stream, a.table, a.nlat, a.steps_add,      \
+                           a.launches_add & 1, steps);                                        \
         break;
         LBM_BLOCK_ROWS(LBM_CASE)
 #undef LBM_CASE

@@ -490,16 +490,14 @@ __global__ __launch_bounds__(BX *T, (kDeepWaves<ST>)) void deep_kernel(const voi
     deep_tile<BX, T, ST, COLL>(src, dst, c, P, tl, xcd_tile(blockIdx.x, tl.ntiles), t, err);
 }
 
-// The deep pass over every lattice of a batch.
+// The deep pass over every lattice of a batch, `steps` steps after the table was
+// written, from the buffers of this parity.
 template <int BX, int T, int ST, int COLL>
-__global__ __launch_bounds__(BX *T, (kDeepWaves<ST>)) void batch_deep_kernel(const BatchEntry *__restrict__ table,
-                                                           int nlat,
-                                                           const long long *__restrict__ d_ctr,
-                                                           long long steps_add, int launches_add)
+__global__ __launch_bounds__(BX *T, (kDeepWaves<ST>)) void batch_deep_kernel(
+    const BatchEntry *__restrict__ table, int nlat, long long steps, int parity)
 {
-    const BatchPos pos = batch_pos(d_ctr, steps_add, launches_add);
     const BatchTile k = batch_tile<&BatchEntry::tile0_4, &BatchEntry::tl4>(
-        table, nlat, xcd_tile(blockIdx.x, gridDim.x), pos.steps, pos.parity);
+        table, nlat, xcd_tile(blockIdx.x, gridDim.x), steps, parity);
     const auto P = in_scalar_registers(Phys<typename Store<ST>::R>(k.c));
     deep_tile<BX, T, ST, COLL>(k.src, k.dst, k.c, P, k.tl, k.tile, k.t, k.err);
 }
@@ -537,8 +535,8 @@ hipError_t batch_deep_launch_bx(const BatchArgs &a)
     switch (a.bx) {
 #define LBM_CASE(BX)                                                                          \
     case BX:                                                                                  \
-        hipLaunchKernelGGL((batch_deep_kernel<BX, T, ST, COLL>), dim3(a.grid), dim3(BX *T), 0, a.stream, a.table, a.nlat, a.ctr,         \
-                           a.steps_add, a.launches_add);                                      \
+        hipLaunchKernelGGL((batch_deep_kernel<BX, T, ST, COLL>), dim3(a.grid), dim3(BX *T),    \
+                           0, a.stream, a.table, a.nlat, a.steps_add, a.launches_add & 1);    \
         break;
         LBM_WIDTHSD(LBM_CASE)
 #undef LBM_CASE

@@ -544,8 +544,8 @@ __device__ __forceinline__ void collide_mrt(R d[kQ], R rho, R ux, R uy, R Jx, R 
         // sums and differences of opposite pairs shared by the moments (the
         // momentum's with velocity()), rho u = J, and the stress rows' r =
         // omega J + 2 (1 - omega/2) F: 29 operations less.  (The 1/6 and 1/12
-        // of the last lines as multiply-adds take four less again, but all
-        // populations of a cell then round the same way: 1.03 of the error.)
+        // of the last lines as multiply-adds take four less again, but
+        // measured 1.03 of the error.)
         const R s13 = d[1] + d[3], s24 = d[2] + d[4], s57 = d[5] + d[7], s68 = d[6] + d[8];
         const R d13 = d[1] - d[3], d24 = d[2] - d[4], a57 = d[5] - d[7], b68 = d[6] - d[8];
         const R ax = s13 + s24, dg = s57 + s68, px = a57 - b68, py = a57 + b68;
@@ -1724,7 +1724,8 @@ struct SweepArgs {
 };
 
 // Arguments of a batched launch: where it starts (batch_pos: counters in
-// device memory, or nullptr, plus the steps and launches to add).
+// device memory, or nullptr, plus the steps and launches to add; the long
+// passes, which are never captured, have no counters).
 struct BatchArgs {
     const BatchEntry *table;
     int nlat;
