@@ -308,7 +308,8 @@ def run_batch(args):
     one batched launch per four steps, two or one, as the autotuner finds
     fastest (--fusion 1: single steps only, replayed as 8-step HIP graphs), with
     FP32-shifted storage.  Beside it, the same lattices in FP64 stepped each on
-    its own (the plain path: one launch per lattice per two steps)."""
+    its own (the plain path: one launch per lattice per four steps, in the form
+    the library picks for it)."""
     import torch
     from paper_2003_07968_amd import lbm
     from paper_2003_07968_amd import workloads as W
@@ -347,22 +348,22 @@ def run_batch(args):
         err(f"timed {args.steps} batched steps: {gpu_ms:.2f} ms")
 
         # the plain path on the same lattices: FP64 storage, each lattice on
-        # its own (two steps per launch)
-        seq_steps = 2 * max(4, args.steps // 20)
+        # its own (four steps per launch, as the batch)
+        seq_steps = 4 * max(2, args.steps // 40)
         plain = []
         for p, r in cases:
             q = dict(p)
             q["storage"], q["rho_ref"] = 0, 0.0
             plain.append(lbm.Lattice(q, r))
         for lat in plain:
-            lat.step(2)
+            lat.step(4)
         torch.cuda.synchronize()
         e2 = torch.cuda.Event(enable_timing=True)
         e3 = torch.cuda.Event(enable_timing=True)
         e2.record(stream)
-        for _ in range(seq_steps // 2):
+        for _ in range(seq_steps // 4):
             for lat in plain:
-                lat.step(2)
+                lat.step(4)
         e3.record(stream)
         torch.cuda.synchronize()
         plain_ms = e2.elapsed_time(e3)
