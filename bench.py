@@ -110,16 +110,17 @@ DTYPE = {"f64": "f64", "f32": "f32 (FP32-shifted storage)",
          "f16": "f32 arithmetic, f16-shifted storage",
          "f16l": "f32 arithmetic, f16 storage with per-cell f32 reference"}
 # What limits each dominant kernel, from the committed counter profiles
-# (profiles/deep_4x2048_counters.md, profiles/pass2_4x2048_sq_counters.md, profiles/pass2_*_4x2048_traffic.md):
+# (profiles/deep_4x2048_counters.md, profiles/short_4x2048_counters.md):
 # counter-measured HBM bytes against a plain device copy, and VALU issue time
 # (SQ_INSTS_VALU x 4 cycles per wave64 instruction over 1024 SIMDs at 2.4 GHz)
-# against the launch time.
+# against the launch time.  Reported while the counter record is current.
 LIMITER = {
-    ("deep", "f64"): "hbm and latency: 1.02x the algorithmic bytes at 5.2 TB/s, a plain device "
-                     "copy's rate; VALU issue 51% of the launch (63% at the 1.96 GHz that FP64 "
-                     "arithmetic holds), 28% of wave-cycles waiting at four waves per SIMD "
+    ("deep", "f64"): "hbm and latency: 1.02x the algorithmic bytes at 4.9 to 5.1 TB/s, near a "
+                     "plain device copy's rate; VALU issue 52 to 54% of the launch (two thirds at "
+                     "the 1.96 GHz that FP64 arithmetic holds), a quarter of the wave-cycles "
+                     "waiting at four waves per SIMD "
                      "(profiles/deep_4x2048_counters.md)",
-    ("deep", "f32"): "valu: FP32 arithmetic issue 94% of the launch; HBM 4.4 TB/s, 1.03x the "
+    ("deep", "f32"): "valu: FP32 arithmetic issue 92 to 94% of the launch; HBM 4.3 TB/s, 1.03x the "
                      "algorithmic bytes (profiles/deep_4x2048_counters.md)",
     ("deep", "f16"): "valu: more than one FP32 instruction per four cycles of every SIMD; HBM "
                      "2.4 TB/s, 1.05x the algorithmic bytes (profiles/deep_4x2048_counters.md)",
@@ -127,17 +128,18 @@ LIMITER = {
                       "2.1 TB/s, 1.05x the algorithmic bytes (profiles/deep_4x2048_counters.md)",
     ("pass2", "f64"): "hbm and latency: 1.06x the algorithmic bytes at about 5.5 TB/s, above a "
                       "plain device copy's rate and about 95% of the stream probe of the same "
-                      "access pattern (roofline.per_launch_hbm.stream_probe_gbs); "
-                      "VALU issue 33% of the launch, 40% of wave-cycles waiting on FP64 "
-                      "dependencies at two waves per SIMD; a third wave per SIMD measured no "
-                      "faster (profiles/pass2_4x2048_sq_counters.md)",
-    ("pass2", "f32"): "hbm and issue: 1.06x the algorithmic bytes at about 5.3 TB/s, a plain "
-                      "device copy's rate; VALU issue 61% of the launch "
-                      "(profiles/pass2_4x2048_sq_counters.md)",
-    ("pass2", "f16"): "valu: FP32 arithmetic issue 83% of the launch; HBM about 3.4 TB/s, 1.03x "
-                      "the algorithmic bytes (profiles/pass2_4x2048_sq_counters.md)",
-    ("pass2", "f16l"): "valu: FP32 arithmetic issue 90% of the launch; HBM about 3.2 TB/s, 1.05x "
-                       "the algorithmic bytes (profiles/pass2_4x2048_sq_counters.md)",
+                      "access pattern (roofline.per_launch_hbm.stream_probe_gbs); VALU issue "
+                      "30% of the launch, 27% of wave-cycles at wait counts or barriers "
+                      "(profiles/short_4x2048_counters.md)",
+    ("pass2", "f32"): "hbm and issue: 1.06x the algorithmic bytes at about 5.2 TB/s, a plain "
+                      "device copy's rate; VALU issue 59% of the launch "
+                      "(profiles/short_4x2048_counters.md)",
+    ("pass2", "f16"): "valu: FP32 arithmetic issue 82% of the launch; HBM about 3.5 TB/s, 1.03x "
+                      "the algorithmic bytes (profiles/short_4x2048_counters.md)",
+    ("pass2", "f16l"): "valu: FP32 arithmetic issue 90% of the launch; HBM about 3.3 TB/s, 1.05x "
+                       "the algorithmic bytes (profiles/short_4x2048_counters.md)",
+    ("step", "f64"): "hbm: 1.01x the algorithmic bytes at 5.8 TB/s, 99% of the stream probe of "
+                     "the same access pattern (profiles/short_4x2048_counters.md)",
 }
 
 
@@ -189,6 +191,11 @@ def valu_roofline(kernel, storage, launch_ms, shape=None):
     return {"unit": "G wave64 VALU instructions/s", "achieved": round(achieved, 1),
             "peak": VALU_PEAK_GIPS, "frac": round(achieved / VALU_PEAK_GIPS, 4),
             "insts_per_launch": rec["valu_insts_per_launch"]}
+
+
+def limiter(kernel, storage, shape=None):
+    """LIMITER's text while the counters it rests on are current, or None."""
+    return LIMITER.get((kernel, storage)) if counter_record(kernel, storage, shape) else None
 
 
 def copy_calibration():
@@ -719,7 +726,7 @@ def precision_rates(f64_mlups):
                    "roofline_frac": round(achieved / HBM_PEAK_GBS, 4),
                    "per_launch_hbm_frac": round(achieved / upl / HBM_PEAK_GBS, 4),
                    "valu": valu_roofline(r["kernel"], st, r["launch_ms"]),
-                   "limiter": LIMITER.get((r["kernel"], st))}
+                   "limiter": limiter(r["kernel"], st)}
     return out
 
 
@@ -830,7 +837,7 @@ def main():
             "kernel": f"{res['kernel_name']}, {args.storage} storage, {args.collision})",
             "kernel_avg_ms": round(res["launch_ms"], 5),
             "updates_per_launch_per_cell": upl,
-            "limiter": LIMITER.get((kernel, args.storage)) if counters else None,
+            "limiter": limiter(kernel, args.storage, shape_used) if counters else None,
             "valu": (valu_roofline(kernel, args.storage, res["launch_ms"], shape_used)
                      if counters else None),
             "per_launch_hbm": {

@@ -469,7 +469,7 @@ bool make_tiles4(int nx, int ny, const FourShape &f, Tiles *tl)
 }
 
 // Predicted times, in us per launch (measured on square lattices of 16 to 8192
-// and 2048 x 8192 cells, BGK; the MRT collision takes 1.1 to 1.2 times as
+// and 2048 x 8192 cells, BGK; the MRT collision takes 1.1 to 1.25 times as
 // long in either form).
 //
 // Deep pass: a CU runs kDeepSteps x 256 threads at once (twice that with FP32
@@ -513,10 +513,13 @@ struct LatticeSizes {
 // times.  Where the two come out within 15% the deep pass is taken, whose
 // prediction is the higher one on small lattices (512^2 FP64: deep 35
 // predicted, 26 measured; block 33.5 and 29).  So one square lattice goes
-// to the block pass up to about 200k cells in FP64 and 450k otherwise
-// (measured, us per step, deep / block: FP64 64^2 4.0 / 1.7, 200^2 4.5 / 2.1,
-// 517 x 301 6.1 / 4.5, 512^2 6.5 / 7.3; FP32 64^2 3.9 / 1.5, 512^2 5.6 / 4.7,
-// 700^2 6.8 / 6.7, 1024^2 8.9 / 13.4).
+// to the block pass up to 396^2 in FP64 and the per-cell mode, and up to 576^2
+// in FP32 and FP16, but for 487^2 to 510^2 (FP16: 528^2), where the deep pass
+// comes out just within the margin.  Measured, us per step, deep / block: FP64
+// 64^2 4.0 / 1.7, 200^2 4.5 / 2.1, 517 x 301 6.1 / 4.5, 512^2 6.5 / 7.3; FP32
+// 64^2 3.9 / 1.5, 512^2 5.6 / 4.7, 700^2 6.8 / 6.7, 1024^2 8.9 / 13.4.  Long
+// narrow lattices (16 x 16000 to 6000 x 24, every mode, MRT too) took at most
+// 0.92 of the two-step pass's time in the form chosen, 0.57 on average.
 bool four_shape(const LatticeSizes &z, int storage, int cus, FourShape *out)
 {
     out->us = -1.0;

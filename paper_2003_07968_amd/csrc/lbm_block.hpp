@@ -37,7 +37,7 @@ struct BlockLds {
 };
 
 // Waves per SIMD the block pass is compiled for: as many whole workgroups of
-// RH / 2 waves as fit a CU's 32 waves, or in FP64, which needs up to 88
+// RH / 2 waves as fit a CU's 32 waves, or in FP64, which needs up to 80
 // registers, 24 (one workgroup of 32 rows).
 template <int ST, int RH>
 constexpr int kBlockWaves = (ST == LBM_STORE_F64 ? (RH == 32 ? 16 : 24) : 32) / (RH / 2) * (RH / 2) / 4;

@@ -15,7 +15,7 @@
 // Why a step per wave: the two-step pass holds both steps in one thread (186
 // registers in FP64); a third step would not fit, and its two steps wait for
 // each other at three barriers a row.  Here a thread holds one step's rows
-// (at most 128 registers in FP64, 64 in FP32 arithmetic), all steps of a row
+// (125 registers in FP64, 64 in FP32 and FP16, 73 per cell), all steps of a row
 // run at once, and one barrier per row is enough: in iteration m a step pulls
 // what the previous step wrote in iteration m - 1 and writes what the next
 // step pulls in iteration m + 1.
@@ -35,15 +35,22 @@
 // halo columns and rows on each side, and n rows take n + 6T - 3 iterations.
 //
 // What bounds it (T = 4, 2048 x 8192, one MI355X; the two-step pass on the
-// same lattice in parentheses): FP64 143 G cell updates/s (73), FP32 248
-// (134), FP16 260 (186), per-cell FP16 185 (148).  A row update is 120
+// same lattice in parentheses): FP64 140 G cell updates/s (74), FP32 242
+// (134), FP16 255 (185), per-cell FP16 186 (144).  A row update is 129
 // (FP64), 125 (FP32), 139 (FP16) or 192 (per-cell) VALU instructions per wave.
-// FP32 and the FP16 modes are at their issue rate (0.94 to 1.1 of one
+// FP32 and the FP16 modes are at their issue rate (0.94 to 1.11 of one
 // instruction per four cycles of every SIMD at 2.4 GHz).  FP64, with 16 waves
-// per CU, issues at 0.51 of it, at a clock that FP64 arithmetic on all CUs
-// holds at 1.96 GHz, and waits 28% of its wave-cycles; its HBM traffic, 1.02
-// times one read and one write of the populations per launch, runs at 5.2
-// TB/s, a plain copy's rate.
+// per CU, issues at 0.54 of it, at a clock that FP64 arithmetic on all CUs
+// holds at 1.96 GHz, and waits 25% of its wave-cycles; its HBM traffic, 1.02
+// times one read and one write of the populations per launch, runs at 5.05
+// TB/s, near a plain copy's rate (5.2).
+//
+// The MRT collision: FP64 117, FP32 197, FP16 210, per-cell 152.  It needs more
+// registers than there are: four steps spill 9 to 12 vector registers in FP64
+// (up to 44 bytes of scratch a lane, reloaded in the row loop) and 7 in FP32
+// and FP16, and 22 to 82 scalar ones.  BGK spills no vector registers; scalar
+// ones, into vector lanes, 2 (FP64; batched 7) and 11 (FP32, FP16; batched
+// 28).  The per-cell mode, compiled for 128 registers, spills none.
 //
 // What the issue rate needed, each measured on that lattice in FP64:
 //   LDS addressed by byte offset from four registers (the compiler kept an
