@@ -147,7 +147,11 @@ lbm_status lbm_init(const lbm_params *params, void *d_workspace, size_t workspac
                     void *hip_stream, lbm_handle **out);
 
 /* Enqueue nsteps >= 0 time steps (asynchronous).  Returns LBM_ERR_DEVICE if a
- * launch fails; domain errors surface at lbm_sync. */
+ * launch fails; domain errors surface at lbm_sync.  A call may be recorded in
+ * a graph by stream capture: every launch of one or two steps exchanges the two
+ * population buffers, so replays of a call of an even number of them (one per
+ * pair of steps and one for an odd step) go on from their own result.  Longer
+ * passes are then recorded in pairs, which keeps that. */
 lbm_status lbm_step(lbm_handle *h, int64_t nsteps);
 
 /* Wait for the handle's stream and return the sticky status. */

@@ -734,6 +734,19 @@ bool one_launch(const FourShape &f, int64_t steps)
     return steps >= kDeepSteps || (f.tails >> steps & 1u) != 0;
 }
 
+// How many of a call's first steps the long passes may take: all, or while
+// the stream is being captured as many as an even number of four-step launches
+// takes.  Every launch exchanges the two buffers, so the parity of the launches
+// decides whether a graph that is replayed goes on from its own result or takes
+// the same steps again: it stays that of the one- and two-step launches.
+int64_t long_steps(hipStream_t stream, int64_t nsteps)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess || st == hipStreamCaptureStatusNone)
+        return nsteps;
+    return nsteps / (2 * kDeepSteps) * (2 * kDeepSteps);
+}
+
 template <int ST>
 hipError_t launch_long(const SweepArgs &a, bool block, int steps)
 {
@@ -1272,8 +1285,9 @@ lbm_status lbm_step(lbm_handle *h, int64_t nsteps)
     }
     int64_t k = 0;
     if (h->fuse == 2) {
-        while (h->four && k < nsteps) {
-            const int n = (int)std::min<int64_t>(kDeepSteps, nsteps - k);
+        const int64_t until = h->four ? long_steps(h->stream, nsteps) : 0;
+        while (k < until) {
+            const int n = (int)std::min<int64_t>(kDeepSteps, until - k);
             if (!one_launch(h->shape4, n)) break;
             hipError_t e = run_four(h, h->cur, h->nxt, n);
             if (e != hipSuccess) return dev_fail(h, e, "launching the four-step kernel");
@@ -1757,12 +1771,17 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps)
         b->ctr_steps = s0 + kGraphSteps;
         b->ctr_launches = l0 + kGraphSteps / per;
     }
+    const int fuse = batch_fuse(b);
+    const int64_t until = per == kDeepSteps ? long_steps(b->stream, nsteps) : 0;
     while (done < nsteps) {
         const int64_t left = nsteps - done;
-        const int k = left >= per ? per
-                                  : (batch_long(b, (int)left)     ? (int)left
-                                     : left >= batch_fuse(b) ? batch_fuse(b)
-                                                             : 1);
+        int k = left >= fuse ? fuse : 1;
+        if (done < until) {
+            if (left >= kDeepSteps)
+                k = kDeepSteps;
+            else if (batch_long(b, (int)left))
+                k = (int)left;
+        }
         const hipError_t e =
             batch_launch_steps(b, k, nullptr, b->steps_since_upload + done,
                                (int)((b->launches_since_upload + launches) & 1));
