@@ -96,3 +96,21 @@ def test_a_batch_returns_to_the_library_choice_and_to_a_tuned_pass():
         batch.step(9)
         ref.step(32)
         assert lat.t == 32 and torch.equal(lat.populations(), ref.populations())
+
+
+def test_a_large_batch_whose_shape_is_chosen_by_a_sample():
+    # more members than the choice looks at, the largest at a place that it
+    # skips: bitwise the single steps' results
+    require_gpu()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        sizes = [(16 + k % 23, 16 + k % 19) for k in range(600)]
+        sizes[301] = (700, 500)
+        lats = [_lattice(nx, ny, "f32") for nx, ny in sizes]
+        batch = _batch(*lats)
+        assert batch.get_pass()[0] == 4
+        batch.step(11)
+        for k in (0, 1, 2, 300, 301, 302, 450, 599):
+            ref = _lattice(*sizes[k], "f32", launch=(256, 8))
+            ref.step(11)
+            lats[k].sync()
+            assert torch.equal(lats[k].populations(), ref.populations()), sizes[k]

@@ -2,11 +2,10 @@
 the library picks for it: bitwise the single steps' results, and no slower than
 the forms of one and two steps per launch.
 
-Times: medians of seven samples of 40 calls between two events.  A call of one
+Times: the best of seven samples of 40 calls between two events.  A call of one
 to three steps may take 1.25 times as long as in those forms (the choice rests
 on predictions that are off by up to 10%, twice, and the two sides are timed
 apart); computing a four-step halo for every step took 1.3 to 2 times as long."""
-import statistics
 
 import pytest
 import torch
@@ -57,7 +56,7 @@ def _us(call, stream):
         e1.record(stream)
         e1.synchronize()
         samples.append(e0.elapsed_time(e1) * 1e3 / 40)
-    return statistics.median(samples)
+    return min(samples)
 
 
 @pytest.mark.parametrize("storage,sizes", CASES,
