@@ -2,7 +2,8 @@
 
 The device code is split into translation units that compile in parallel:
 csrc/lbm_inst.hip once per storage mode and kernel family (the single-step
-sweeps, and the two-step pass), csrc/lbm.hip (host runtime and C ABI) and
+sweeps, the two-step pass, the passes of four steps and of three), csrc/lbm.hip
+(host runtime and C ABI) and
 csrc/server.cpp (the serving loop).  Objects go to _build/ beside this file;
 the library is linked in-tree so that it travels with the source tree.
 

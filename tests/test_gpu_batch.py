@@ -33,10 +33,11 @@ def _mixed(storage="f64", count=6, seed=3):
 @pytest.mark.parametrize("fusion", [2, 1])
 @pytest.mark.parametrize("storage", ["f64", "f32", "f16", "f16l"])
 def test_batch_equals_alone(storage, fusion):
-    # eager launches (3 steps: one two-step launch and a single step), then
-    # graph replays (8-step graphs) with checks and eager work in between,
-    # one single step that flips the launch parity, then remainders: every
-    # lattice bitwise equal to its solo run after each stage.
+    # remainders, whole groups of eight steps with checks and eager work in
+    # between, one single step that flips the launch parity, then remainders:
+    # every lattice bitwise equal to its solo run after each stage.  One step
+    # per launch: replays of the captured 8-step graphs; otherwise the long
+    # passes (test_gpu_graphs.py has the two-step pass's graphs)
     require_gpu()
     cases = _mixed(storage)
     solo = [gpu_lattice(p, r) for p, r in cases]
@@ -218,7 +219,8 @@ def test_domain_error_stays_with_its_lattice():
 
 
 def test_batch_on_null_stream_runs_eagerly():
-    # on the legacy null stream no graph is captured; results are the same
+    # on the legacy null stream nothing can be captured; the long passes run as
+    # on any other (test_gpu_graphs.py has the two-step pass there)
     cases = _mixed("f64", count=2, seed=9)
     with torch.cuda.stream(torch.cuda.default_stream()):
         solo = [gpu_lattice(p, r) for p, r in cases]
@@ -236,10 +238,11 @@ def test_batch_on_null_stream_runs_eagerly():
 @pytest.mark.parametrize("fusion", [2, 1])
 @pytest.mark.parametrize("collision", ["bgk", "mrt"])
 def test_graph_replays_match_oracle(oracle, collision, fusion):
-    # 40 batched FP64 steps: five replays of the captured 8-step graph, with
-    # every lattice compared element by element with the CPU oracle after the
-    # first replay and at the end (the graph path against the oracle, not
-    # only against eager launches).
+    # 40 batched FP64 steps, every lattice compared element by element with the
+    # CPU oracle after the first eight and at the end.  One step per launch:
+    # five replays of the captured 8-step graph (against the oracle, not only
+    # against eager launches); otherwise the long passes (test_gpu_graphs.py has
+    # the two-step pass's graphs)
     require_gpu()
     cases = W.batch_case(count=3, seed=21, storage="f64", side_range=(20, 72))
     mates = []

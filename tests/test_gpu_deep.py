@@ -1,10 +1,11 @@
 """The passes of more than two steps per launch that the library takes by
 itself (no launch shape set): bitwise equal to single steps in every storage
-mode with either collision, at sizes around the strip widths of each workgroup
-width, for tiny lattices that wrap inside one tile and for step counts with
-every remainder, alone and batched (graph replays included); and the first
-domain error is the oracle's step and cell whichever step of a pass it falls
-in.  Every comparison is exact: each step runs the single step's routines on
+mode with either collision, from tiny lattices that wrap inside one tile to
+several strips, and for step counts with every remainder, alone and batched
+(launched directly, without graphs); and the first domain error is the oracle's
+step and cell whichever step of a block pass it falls in.  (The library takes
+the block pass at these sizes but for the two largest and two of the batches;
+the other forms have their own tests in test_gpu_pass_forms.py.)  Every comparison is exact: each step runs the single step's routines on
 the same values, rounded to the storage type in between."""
 import numpy as np
 import pytest
@@ -18,9 +19,8 @@ from .helpers import oracle_params
 
 pytestmark = pytest.mark.gpu
 
-# tiny and wrapping; one and two strips of 64-, 128- and 256-column workgroups
-# (50, 114 and 242 columns fit one strip) and of 18-column blocks; several
-# segments, odd row counts
+# tiny and wrapping; one and several columns of blocks (18 cells wide), odd row
+# counts; the last two in the deep pass
 SIZES = [(3, 3), (5, 19), (17, 9), (50, 33), (51, 16), (64, 64), (114, 7), (115, 40), (242, 31),
          (243, 77), (18, 18), (19, 37), (200, 200), (301, 203), (640, 640), (1030, 517)]
 

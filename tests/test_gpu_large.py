@@ -1,6 +1,6 @@
 """Large lattices, beyond what the CPU oracle steps in seconds: 8192 x 8192
-(67 M cells; 9.7 GB of FP64 populations) in the library's default launch
-(two steps per pass, the benchmarked path) and with single steps.
+(67 M cells; 9.7 GB of FP64 populations) in the two-step pass and with single
+steps (test_gpu_full_size_deep.py has the default pass of four steps).
 
 Sampled parity: f(t + s) of sampled cells against the oracle stepping the
 neighbourhood of each cell s times, taken from the GPU's f(t) as a small

@@ -124,9 +124,10 @@ def test_full_size_slab_first_steps(oracle):
 
 @pytest.mark.parametrize("collision", ["bgk", "mrt"])
 def test_full_size_batch_as_benchmarked(oracle, collision):
-    # the benchmark's own form: the four 2048 x 2048 slabs (T_r 0.6 .. 0.9)
-    # in one batch, one launch for all four per two steps, in the launch
-    # shape bench.py uses (BGK, the default line, and MRT, --collision mrt);
+    # the benchmark's two-step form (--fusion 2): the four 2048 x 2048 slabs
+    # (T_r 0.6 .. 0.9) in one batch, one launch for all four per two steps, in
+    # the launch shape bench.py uses (BGK and MRT; the default line's form is in
+    # test_gpu_full_size_deep.py);
     # every lattice compared element by element with the oracle at t = 2 (one
     # two-step launch) and t = 3 (one single step)
     require_gpu()
@@ -161,7 +162,7 @@ def test_full_size_batch_as_benchmarked(oracle, collision):
 
 
 def test_full_size_batch_graph_replays(oracle):
-    # the benchmarked form over 96 steps: twelve replays of the batch's
+    # that form over 96 steps: twelve replays of the batch's
     # captured eight-step graph (four two-step launches each) at full size,
     # every lattice compared with the oracle at the end
     require_gpu()

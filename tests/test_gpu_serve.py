@@ -92,8 +92,8 @@ def test_results_same_alone_and_in_the_mix():
 
 @pytest.mark.parametrize("quantum", [7, 24])
 def test_fp64_jobs_match_oracle(oracle, quantum):
-    # quantum 7 advances each round by launches of its own; quantum 24 also
-    # replays the batches' captured 8-step graphs
+    # quantum 7 leaves a remainder after the four-step launches of each round,
+    # quantum 24 none
     require_gpu()
     jobs = _jobs(3, seed=12, storages=("f64",), sides=(20, 48), steps=(20, 60))
     srv = lbm.Server(arena_bytes=64 << 20, max_resident=4, quantum=quantum)

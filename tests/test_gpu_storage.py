@@ -54,7 +54,8 @@ def test_matches_storage_emulating_oracle(oracle, storage):
 
 @pytest.mark.parametrize("storage", ["f32", "f16", "f16l"])
 def test_full_size_batch_matches_storage_emulating_oracle(oracle, storage):
-    # the benchmark's precision part in its own form: the four 2048 x 2048
+    # the benchmark's two-step form (--fusion 2; the default form is in
+    # test_gpu_full_size_deep.py) in each storage mode: the four 2048 x 2048
     # slabs in one batch, in the launch shape bench.py uses for this storage
     # mode, one batched two-step launch (t = 2) and one single step (t = 3),
     # every lattice against the storage-emulating oracle
